@@ -25,7 +25,8 @@
 //     kept in registers, still a single pass;
 //   streaming (longer sequences): tiles are double buffered in LDS with the next tile
 //     prefetched into registers; the score pass sweeps twice (per-lane statistics, then
-//     the column statistic).
+//     the column statistic). The bf16 output pass of six key tiles or more uses 32x32x16
+//     MFMA tiles and direct loads to LDS (k_attn_stream32).
 // Local-window attention (Sec. "Longformer": a window of w keys around each token and a
 // global first token): query q attends key k < len when |q - k| <= w / 2, or q = 0, or
 // k = 0; the other scores are masked like padded keys. The column max is then taken of
@@ -978,8 +979,8 @@ __device__ __forceinline__ void pv_tile_m(f32x4_t y[MT][4], const f32x4_t acc[MT
 // stored before iteration t's barrier (its buffer was last read by the Q K^T of tile t - 1,
 // issued in iteration t - 2), H~ tile t + 1 after it (its buffer was last read by the P V of
 // tile t - 1 in iteration t - 1, which every wave has finished once it passes the barrier).
-// The bf16 full-attention instance is held to 168 registers (three waves per SIMD), which it
-// meets without spilling; the others need more.
+// The bf16 instance (full attention) is held to 168 registers (three waves per SIMD), which it
+// meets without spilling; the float32 ones need more.
 template <int BF, bool BAND, int MT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu((BF && !BAND) ? 3 : 1))) void k_attn_stream(FwdParams p) {
   using T = typename Elem<BF>::T;
@@ -1073,6 +1074,235 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu((BF &&
         float* yrow = p.Y + ((int64_t)c.b * c.n + row) * c.d_out + c.h * kDHead + c.r16;
 #pragma unroll
         for (int cc = 0; cc < 4; ++cc) yrow[16 * cc] = y[m][cc][i];
+      }
+    }
+}
+
+// ------------------------------------------------------------------ Y = A H~, streaming, bf16
+// 32x32x16 MFMA tiles, 128 queries per block, 32 per wave. What bounds the pass is issue on
+// each SIMD: a 32-key half tile costs a wave 8 MFMAs, 16 exp2, 16 fma and 8 bf16 packs. Next to
+// vector work an MFMA of either shape costs about 8 issue cycles, an exp2 8, another vector
+// instruction 4, so 32x32 tiles halve the matrix cores' share of the issue, but only where
+// every MFMA has vector work beside it: an MFMA that waits in a run of MFMAs costs its full 32
+// cycles (issue probe, per 32 scores of a lane: 586 cycles with one MFMA, two fma, two exp2 and
+// a pack in turn, 771 with the MFMAs in blocks; 16x16 tiles 715 and 826). So half tile h runs
+// as eight slots that are fixed in the source, each one MFMA and the vector work of two scores:
+// the MFMAs are Q K^T of half tile h + 1 and P V of half tile h - 1, the vector work P of h.
+// Each slot then reloads the fragment its MFMA has just used, for half tile h + 2 (K) or h (V).
+//
+// K and H~ tiles (64 keys) are loaded straight into LDS (no registers, no vector work), three
+// buffers each: iteration t reads K tile t + 1 and H~ tile t, which have landed at its barrier,
+// and starts the loads of K tile t + 2 and H~ tile t + 1 into the buffers last read in
+// iteration t - 2, whose reads every wave had consumed before this barrier. 128-byte rows, the
+// 16-byte chunks permuted per row so that each access is free of bank conflicts (measured per
+// permutation): K chunk c of row r at c ^ ((r >> 1) & 7), H~ chunk c at c ^ 2 (r & 1) ^ 4 (r >> 1 & 1).
+__device__ __forceinline__ int k32_swz(int row) { return (row >> 1) & 7; }
+__device__ __forceinline__ int v32_swz(int row) { return ((row & 1) << 1) | ((row & 2) << 1); }
+
+// One direct load of 16 bytes per lane through the buffer descriptor rs (four scalar words)
+// at byte offset off: lane l's bytes land at lds + 16 l, zeros where the offset is out of
+// range. As load_lds16, the kernel does the waiting.
+__device__ __forceinline__ void buffer_load_lds16(u32x4_t rs, uint32_t off, uint32_t lds) {
+  asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(off), "s"(rs), "{m0}"(lds) : "memory");
+}
+
+// Descriptor of the 32 rows from key0 on of a [*, ld] bfloat16 matrix (the head's column slice),
+// as four scalar words; rows at or past n are out of range (as tile_rsrc).
+__device__ __forceinline__ u32x4_t rows32_rsrc(const void* base, int ld, int key0, int n) {
+  const int bytes = max((min(n - key0, 32) - 1) * ld * 2 + kDHead * 2, 0);
+  const uint64_t a = (uint64_t)(uintptr_t)base + (uint64_t)((int64_t)key0 * ld * 2);
+  u32x4_t w;
+  w[0] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+  w[1] = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu));
+  w[2] = (uint32_t)__builtin_amdgcn_readfirstlane(bytes);
+  w[3] = (uint32_t)kBufWord3;
+  return w;
+}
+
+// Keeps the computation of x before this point and what follows behind it.
+template <typename T>
+__device__ __forceinline__ void pin(T& x) { asm volatile("" : "+v"(x)); }
+
+template <bool BAND, int MT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 3 : 2))) void k_attn_stream32(FwdParams p) {
+  constexpr int QB = 128 * MT;
+  constexpr int kTileElems = kTile * kDHead;
+  __shared__ __align__(16) uint16_t smem[6 * kTileElems];  // three K tiles, three H~ tiles
+  const BlockCtx c = block_ctx_q<QB>(p);
+  const int wave = __builtin_amdgcn_readfirstlane(c.wave);
+  const int qw = c.qt * QB + wave * 32 * MT;  // the wave's first query
+  const int r32 = c.lane & 31, hf = c.lane >> 5, i16 = c.lane & 15;
+  const int64_t off = (int64_t)c.b * c.n * c.d_out + c.h * kDHead;
+  const uint16_t* Qb = static_cast<const uint16_t*>(p.Q) + off;
+  const uint16_t* Kb = static_cast<const uint16_t*>(p.K) + off;
+  const uint16_t* Vb = static_cast<const uint16_t*>(p.Henc) + off;
+  const int nvis = tile_count(c);
+
+  // the wave's direct loads of a tile: rows 8 wave + lane / 8 and 32 further, lane l filling
+  // chunk position l % 8 of its row
+  const int drow = 8 * wave + (c.lane >> 3);
+  const uint32_t koff = (uint32_t)(drow * c.d_out * 2 + (((c.lane & 7) ^ k32_swz(drow)) << 4));
+  const uint32_t voff = (uint32_t)(drow * c.d_out * 2 + (((c.lane & 7) ^ v32_swz(drow)) << 4));
+  const uint32_t dst = lds_addr(smem) + 1024u * wave;
+  auto load_tile = [&](const uint16_t* base, uint32_t loff, int t, int slot) __attribute__((always_inline)) {
+    const int key0 = tile_at(c, min(t, nvis - 1)) * kTile;
+    const uint32_t to = dst + (uint32_t)slot * (kTileElems * 2);
+    buffer_load_lds16(rows32_rsrc(base, c.d_out, key0, c.n), loff, to);
+    buffer_load_lds16(rows32_rsrc(base, c.d_out, key0 + 32, c.n), loff, to + 4096u);
+  };
+  load_tile(Kb, koff, 0, 0);
+
+  // Q as the B operand of S^T = K Q^T: query qw + 32 m + r32, d = 16 ks + 8 hf .. + 7
+  bf16x8_t qf[MT][4];
+  float ncq[MT];
+  int klo[MT], kspan[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const int q = min(qw + 32 * m + r32, c.n - 1);
+    const uint16_t* qrow = Qb + (int64_t)q * c.d_out + 8 * hf;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) qf[m][ks] = *reinterpret_cast<const bf16x8_t*>(qrow + 16 * ks);
+    ncq[m] = -p.row_c[((int64_t)c.b * p.H + c.h) * c.n + q];
+    klo[m] = kspan[m] = 0;
+    if (BAND) query_window(c, qw + 32 * m + r32, klo[m], kspan[m]);
+  }
+
+  load_tile(Kb, koff, 1, 1);  // not waited for before the first scores
+  load_tile(Vb, voff, 0, 3);
+
+  // fragment addresses (elements) in a tile: K row r32 (of a half tile), d = 16 ks + 8 hf; H~
+  // rows 4 hf + i16 / 4 (+ 8, 16 pp, 32 per half tile), columns 32 cc + 16 (lane / 16 % 2) + 4 (i16 % 4)
+  int ka[4], va[2];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) ka[ks] = r32 * kDHead + (((2 * ks + hf) ^ k32_swz(r32)) << 3);
+#pragma unroll
+  for (int cc = 0; cc < 2; ++cc) {
+    const int row = 4 * hf + (i16 >> 2), col = 32 * cc + 16 * ((c.lane >> 4) & 1) + 4 * (i16 & 3);
+    va[cc] = row * kDHead + ((((col >> 3) ^ v32_swz(row)) << 3) | (col & 7));
+  }
+  const uint16_t *kp[4], *vp[2];  // the lane's addresses in the tiles being read
+  auto set_tiles = [&](int kslot, int vslot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) kp[ks] = smem + (ka[ks] + kslot * kTileElems);
+#pragma unroll
+    for (int cc = 0; cc < 2; ++cc) vp[cc] = smem + (va[cc] + (3 + vslot) * kTileElems);
+  };
+  auto read_k = [&](int half, int ks) __attribute__((always_inline)) {
+    return *reinterpret_cast<const bf16x8_t*>(kp[ks] + half * 32 * kDHead);
+  };
+  auto read_v = [&](int half, int pp, int cc) __attribute__((always_inline)) {
+    const uint16_t* v = vp[cc] + (32 * half + 16 * pp) * kDHead;
+    const uint2 lo = lds_read_tr16(v), hi = lds_read_tr16(v + 8 * kDHead);
+    return __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
+  };
+
+  const f32x16_t zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16_t y[MT][2], s0[MT], s1[MT];
+  u32x4_t pa[MT][2], pb[MT][2];  // P of a half tile, 16 keys each, as A operands
+  bf16x8_t kf[4], vf[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {  // the first P V multiplies zeros
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      y[m][i] = zero;
+      pb[m][i] = u32x4_t{0u, 0u, 0u, 0u};
+    }
+    vf[i][0] = vf[i][1] = __builtin_bit_cast(bf16x8_t, pb[0][0]);
+  }
+  wait_vmcnt<4>();  // K tile 0 (and Q)
+  stage_barrier();
+  set_tiles(0, 0);
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) kf[ks] = read_k(0, ks);
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+      s0[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[m][ks], ks == 0 ? zero : s0[m], 0, 0, 0);
+    kf[ks] = read_k(1, ks);
+  }
+
+  // masked scores of half tile `half` of tile kt: reg i is key 64 kt + 32 half + 8 (i / 4) + 4 hf + i % 4
+  auto mask = [&](f32x16_t (&s)[MT], int kt, int half) __attribute__((always_inline)) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int key = kt * kTile + 32 * half + 8 * (i >> 2) + 4 * hf + (i & 3);
+        const bool ok = BAND ? (unsigned)(key - klo[m]) <= (unsigned)kspan[m] || key == 0 : key < c.len;
+        s[m][i] = ok ? s[m][i] : -INFINITY;
+      }
+  };
+  // Half tile h: P of cur into pout, Q K^T of half tile h + 1 into nxt, P V of half tile h - 1
+  // (pi, vf); K half tile h + 2 and H~ half tile h are `half` of the tiles that set_tiles chose.
+  auto step = [&](f32x16_t (&cur)[MT], f32x16_t (&nxt)[MT], const u32x4_t (&pi)[MT][2], u32x4_t (&po)[MT][2], int half)
+      __attribute__((always_inline)) {
+    float e0 = 0.f, e1 = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8 * MT; ++j) {
+      const int i = j / (2 * MT), m = (j >> 1) % MT, pp = i >> 1, cc = i & 1;
+      if (j % 2 == 0) {
+        nxt[m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], qf[m][i], i == 0 ? zero : nxt[m], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);  // the reload takes the registers the MFMA has read
+        if (m == MT - 1) kf[i] = read_k(half, i);
+      } else {
+        y[m][cc] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, pi[m][pp]), vf[pp][cc], y[m][cc],
+                                                           0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (m == MT - 1) vf[pp][cc] = read_v(half, pp, cc);
+      }
+      const int n = j >> 3, k = j & 7;  // scores 2 k, + 1 of query tile n
+      const float x0 = __fmaf_rn(cur[n][2 * k], kLog2eOver8, ncq[n]);
+      const float x1 = __fmaf_rn(cur[n][2 * k + 1], kLog2eOver8, ncq[n]);
+      if (j > 0) {  // the pair before: its exp2 results are not waited for
+        uint32_t w = pack_bf16x2(e0, e1);
+        pin(w);
+        po[(j - 1) >> 3][((j - 1) >> 2) & 1][(j - 1) & 3] = w;
+      }
+      e0 = exp2_fast(x0);
+      e1 = exp2_fast(x1);
+      pin(e0);
+      pin(e1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    po[MT - 1][1][3] = pack_bf16x2(e0, e1);
+  };
+  int b0 = 0, b1 = 1, b2 = 2;  // buffers of tiles t, t + 1, t + 2
+#pragma clang loop unroll(disable)
+  for (int t = 0; t < nvis; ++t) {
+    wait_vmcnt<0>();
+    stage_barrier();
+    load_tile(Kb, koff, t + 2, b2);
+    load_tile(Vb, voff, t + 1, 3 + b1);
+    set_tiles(b1, b0);
+    const int kt = tile_at(c, t);
+    const bool masked = BAND ? !band_tile_inside(c, kt, qw, 32 * MT) : c.len - kt * kTile < kTile;  // wave-uniform
+    if (__builtin_expect(masked, 0)) mask(s0, kt, 0);
+    step(s0, s1, pb, pa, 0);
+    if (__builtin_expect(masked, 0)) mask(s1, kt, 1);
+    step(s1, s0, pa, pb, 1);
+    const int b = b0;
+    b0 = b1;
+    b1 = b2;
+    b2 = b;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+      y[m][i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, pb[m][i >> 1]), vf[i >> 1][i & 1],
+                                                            y[m][i & 1], 0, 0, 0);
+  wait_vmcnt<0>();  // the trailing loads have landed before the wave ends
+  // y[m][cc][i] = Y[query qw + 32 m + 8 (i / 4) + 4 hf + i % 4][column 32 cc + r32]
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int row = qw + 32 * m + 8 * (i >> 2) + 4 * hf + (i & 3);
+      if (row < c.n) {
+        float* yrow = p.Y + ((int64_t)c.b * c.n + row) * c.d_out + c.h * kDHead + r32;
+        yrow[0] = y[m][0][i];
+        yrow[32] = y[m][1][i];
       }
     }
 }
@@ -1426,8 +1656,18 @@ hipError_t launch_attn_band(const FwdParams& p, hipStream_t s) {
     if (nt <= 1) return launch_stage_kernel((k_attn_res<1, 1, BAND>), grid, blk, 0, s, p);
     else if (nt <= 2) return launch_stage_kernel((k_attn_res<1, 2, BAND>), grid, blk, 0, s, p);
     else if (nt <= 4) return launch_stage_kernel((k_attn_res<1, 4, BAND>), grid, blk, 0, s, p);
-    else return launch_stage_kernel((k_attn_stream<1, BAND, 2>), dim3((unsigned)(((p.n + 127) / 128) * p.H * p.B)),
-                                    blk, 0, s, p);
+    // five key tiles: the 16x16 kernel is the faster one (16 x 300 tokens: 13.2 against 14.2 us;
+    // from six on the 32x32 one is: 16 x 512, 16 heads 25.2 -> 23.5)
+    else if (!BAND && nt <= 5)
+      return launch_stage_kernel((k_attn_stream<1, false, 2>), dim3((unsigned)(((p.n + 127) / 128) * p.H * p.B)), blk, 0, s, p);
+    const int64_t q128 = (p.n + 127) / 128, wide = (q128 + 1) / 2 * p.H * p.B;
+    // 256 queries per block (64 per wave) halve the LDS reads and tile loads per score, which
+    // is what a long call is paid in once the card runs at its power limit (4096 tokens: 196 ->
+    // 178 us), where they fill two blocks per CU and waste little on the last one; a smaller
+    // grid is faster in blocks of 128 (8 x 640 tokens: 16.2 against 22.2 us)
+    if (!BAND && wide >= 2 * 256 && (q128 % 2 == 0 || q128 >= 15))
+      return launch_stage_kernel((k_attn_stream32<false, 2>), dim3((unsigned)wide), blk, 0, s, p);
+    return launch_stage_kernel((k_attn_stream32<BAND, 1>), dim3((unsigned)(q128 * p.H * p.B)), blk, 0, s, p);
   } else {
     if (nt <= 1) return launch_stage_kernel((k_attn_res<0, 1, BAND>), grid, blk, 0, s, p);
     else if (nt <= 2) return launch_stage_kernel((k_attn_res<0, 2, BAND>), grid, blk, 0, s, p);

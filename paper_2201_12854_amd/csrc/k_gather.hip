@@ -271,9 +271,6 @@ __device__ __forceinline__ float4 lds_read4(uint32_t addr) {
   return float4{};
 #endif
 }
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)p;  // address-space cast
-}
 
 // Entry pairs are read through a pointer that advances one round (LPR entries) at a time,
 // up to three rounds past the end of a part: those entries are masked, and the list buffer
@@ -699,14 +696,6 @@ __global__ __launch_bounds__(kSatThreads) void k_saturated(FwdParams p) {
 // last chunk: the prepared W_v^T is zero there.
 constexpr int kSatStages = 3;
 
-// s_waitcnt for at most n outstanding vector memory operations (gfx9 encoding: vmcnt in
-// bits 3:0 and 15:14; expcnt and lgkmcnt left at their maxima, i.e. not waited for).
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
-}
-
 // One direct global-to-LDS load of 16 bytes per lane: lane l's bytes land at lds + 16 l
 // (lds wave-uniform, in M0: an input operand bound to that register, so the compiler sets
 // it and knows it is read). Issued through inline assembly so that the compiler does not
@@ -714,14 +703,6 @@ __device__ __forceinline__ void wait_vmcnt() {
 // loads issued after the one it needs) and publishes them with a barrier.
 __device__ __forceinline__ void load_lds16(const void* g, uint32_t lds) {
   asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(lds) : "memory");
-}
-
-// Block barrier without a memory fence: LDS written by the direct loads is published by the
-// explicit wait before it, and the compiler may not move memory operations across it.
-__device__ __forceinline__ void stage_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
 }
 
 template <int BF, int NTW, int MTW, int ST, int WN = 2>

@@ -1,0 +1,71 @@
+"""Attention passes against plain torch in float64 at the edges of their tiles: Y = A H~ with the
+library's own H~ (exported), and the column statistic m, over lengths, windows and grid sizes
+that choose each kernel."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    import paper_2201_12854_amd as mca
+
+# (batch, n, heads, window, ragged): the resident kernels' last lengths, the 16x16 output pass
+# (5 key tiles), then 32x32 tiles with partial query and key tiles in blocks of 128 queries, and
+# grids that fill two blocks per CU in blocks of 256 (whole, and with a short last block)
+SHAPES = [(2, 64, 4, 0, True), (2, 256, 4, 0, True), (2, 257, 4, 0, True), (1, 320, 4, 0, False),
+          (2, 321, 4, 0, True), (1, 384, 8, 0, False), (2, 449, 4, 0, True), (1, 513, 4, 0, False),
+          (2, 577, 4, 0, True), (2, 300, 4, 64, True), (2, 333, 4, 2, True), (1, 1057, 4, 256, False),
+          (64, 500, 8, 0, True), (9, 1900, 8, 0, True)]
+
+
+def _reference(Q, K, H, lens, heads, window):
+    """Y, sum_j A |H|, and m per key (|S_i| A under a window), float64, one batch row at a time."""
+    B, n, d = Q.shape
+    i = torch.arange(n, device=Q.device)
+    for b in range(B):
+        L = int(lens[b])
+        ok = (i < L)[None, :].expand(n, n)
+        if window:
+            ok = ok & (((i[:, None] - i[None, :]).abs() <= window // 2) | (i[:, None] == 0) | (i[None, :] == 0))
+        size = ok.sum(1).double()[:, None] if window else 1.0
+        Y = torch.empty(n, d, dtype=torch.float64, device=Q.device)
+        Ya = torch.empty_like(Y)
+        m = torch.zeros(n, dtype=torch.float64, device=Q.device)
+        for h in range(heads):
+            c = slice(64 * h, 64 * h + 64)
+            S = Q[b, :, c].double() @ K[b, :, c].double().t() / 8
+            A = torch.softmax(S.masked_fill(~ok, -float("inf")), 1)
+            Y[:, c] = A @ H[b, :, c]
+            Ya[:, c] = A @ H[b, :, c].abs()
+            m = torch.maximum(m, (size * A)[:L].amax(0))
+        m[L:] = 0
+        yield b, Y, Ya, m
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("batch,n,heads,window,ragged", SHAPES)
+def test_attention_passes(batch, n, heads, window, ragged, dtype):
+    if dtype == "f32" and batch * n > 4096:
+        pytest.skip("the float32 passes have no variant for large grids")
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    dev, d = torch.device("cuda:0"), 64 * heads
+    rng = np.random.default_rng(1000 * n + heads + window)
+    new = lambda *s: torch.from_numpy(rng.standard_normal(s, dtype=np.float32)).to(dev)  # noqa: E731
+    Q, K, X = (2 * new(batch, n, d)).to(dt), (0.5 * new(batch, n, d)).to(dt), new(batch, n, d).to(dt)
+    W = (0.05 * new(d, d)).to(dt)
+    lens = rng.integers(max(1, n // 2), n + 1, batch) if ragged else np.full(batch, n)
+    r_in = torch.full((batch, n), d, dtype=torch.int32, device=dev)  # H~ = x W_v
+    out = mca.attention_forward(Q, K, X, W, mca.prepare_weights(W), 0.4, 1, heads=heads, r_in=r_in, window=window,
+                                seq_lens=torch.from_numpy(lens.astype(np.int32)).to(dev), export=True)
+    # H~ as the output pass reads it. Each probability is rounded to bfloat16 (2^-9) or float32,
+    # beside the float32 logits' error (below 2^-24 times 64 products of at most about 40) and sums.
+    H = out.encoded.to(dt).double()
+    unit = 2.0 ** -8 if dtype == "bf16" else 1e-5
+    for b, Y, Ya, m in _reference(Q, K, H, lens, heads, window):
+        assert torch.isfinite(out.Y[b]).all()
+        err = (out.Y[b].double() - Y).abs()
+        assert (err <= unit * Ya + 1e-30).all(), (b, (err / Ya).max().item())
+        L = int(lens[b])
+        assert ((out.colmax[b, :L].double() - m[:L]).abs() <= 2e-5 * m[:L] + 2.0 ** -126).all(), b
+        assert (out.colmax[b, L:] == 0).all()
