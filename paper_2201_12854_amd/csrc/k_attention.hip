@@ -1364,7 +1364,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   // sweep 2: per tile (three in flight), per wave and lane row, the lane row's value of key
   // 16 s + r16 at [r16][s]
   __shared__ __align__(16) float cm[3][4][4][16][4];
+  __shared__ int redo;
   const BlockCtx c = block_ctx_q<128>(p);
+  if (c.tid == 0) redo = 0;  // seen behind the first sweep's barriers
   const T* Qb = static_cast<const T*>(p.Q) + (int64_t)c.b * c.n * c.d_out + c.h * kDHead;
   const T* Kb = static_cast<const T*>(p.K) + (int64_t)c.b * c.n * c.d_out + c.h * kDHead;
   const int qw = __builtin_amdgcn_readfirstlane(c.qt * 128 + c.wave * 32);  // the wave's first query
@@ -1439,11 +1441,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   // logit in tile 0 (finite: key 0 is attended by every query), and every later term is
   // added under it, with no check per tile: the terms of a positive sum may exceed 1 without
   // losing relative precision, and only a logit more than 127 log2 units above M would
-  // overflow. If any sum came out non-finite (that, or non-finite scores), the wave runs the
+  // overflow. If any sum came out non-finite (that, or non-finite scores), the block runs the
   // sweep again the careful way: terms added under the current reference as long as a tile's
   // four terms of a query sum to at most 2^16, otherwise (the first tile, and rarely later)
-  // the tile redone with M raised to the running max and the sum rescaled. Both branches
-  // are wave-uniform.
+  // the tile redone with M raised to the running max and the sum rescaled (wave-uniform).
   constexpr float kNoMax = -1e30f;  // below every logit: no attended key seen yet
   constexpr float kRaise = 65536.f;
   float M[8], Ls[8];
@@ -1474,8 +1475,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   bool overflow = false;
 #pragma unroll
   for (int k = 0; k < 8; ++k) overflow |= !(Ls[k] < INFINITY);
-  if (__any(overflow)) {
-    lds_barrier();  // the first sweep is done with both K buffers
+  if (overflow) redo = 1;
+  lds_barrier();  // the first sweep is done with both K buffers
+  if (redo) {     // block-uniform: every wave stages its share of the tiles and meets the barriers
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       M[k] = kNoMax;

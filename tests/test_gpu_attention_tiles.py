@@ -69,3 +69,30 @@ def test_attention_passes(batch, n, heads, window, ragged, dtype):
         L = int(lens[b])
         assert ((out.colmax[b, :L].double() - m[:L]).abs() <= 2e-5 * m[:L] + 2.0 ** -126).all(), b
         assert (out.colmax[b, L:] == 0).all()
+
+
+@pytest.mark.parametrize("window", [0, 128])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_late_logit_past_the_reference(window, dtype):
+    # A few queries meet a logit of 100 (144 log2 units: past a float32 sum under a reference from
+    # the first key tile) at a key far behind, the others see even attention; under the window
+    # only query 0 reaches it.
+    dt, n, heads = (torch.bfloat16 if dtype == "bf16" else torch.float32), 700, 4
+    dev, d = torch.device("cuda:0"), 64 * heads
+    rng = np.random.default_rng(5)
+    Q, K = torch.zeros(1, n, d, device=dev), torch.zeros(1, n, d, device=dev)
+    for i in (0, 3, 130, 695):
+        Q[0, i, :8] = 10.0
+    K[0, 600, :8] = 10.0  # dot 800, logit 100
+    X = torch.from_numpy(rng.standard_normal((1, n, d), dtype=np.float32)).to(dev)
+    W = torch.from_numpy(0.05 * rng.standard_normal((d, d), dtype=np.float32)).to(dev)
+    Q, K, X, W = (v.to(dt) for v in (Q, K, X, W))
+    r_in = torch.full((1, n), d, dtype=torch.int32, device=dev)
+    out = mca.attention_forward(Q, K, X, W, mca.prepare_weights(W), 0.4, 1, heads=heads, r_in=r_in, window=window,
+                                export=True)
+    H = out.encoded.to(dt).double()
+    # the rounding of a float32 logit of 144 log2 units, times ln 2, beside the probabilities'
+    unit = 4 * 0.6931 * 2.0 ** -24 * 145 + (2.0 ** -8 if dtype == "bf16" else 1e-5)
+    for b, Y, Ya, m in _reference(Q, K, H, [n], heads, window):
+        assert ((out.Y[b].double() - Y).abs() <= unit * Ya + 1e-30).all()
+        assert ((out.colmax[b].double() - m).abs() <= (unit - 2.0 ** -8 * (dtype == "bf16") + 2e-5) * m + 2.0 ** -126).all()
