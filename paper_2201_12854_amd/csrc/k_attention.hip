@@ -32,12 +32,15 @@
 // k = 0; the other scores are masked like padded keys. The column max is then taken of
 // |S_q| A[q, k], |S_q| the number of keys query q attends (the count rule's per-row factor
 // n of Eq. 9), and the streaming variants visit only the key tiles a query tile's window
-// reaches, plus tile 0 (all tiles for the tile holding query 0).
+// reaches, plus tile 0 (float32, and rows of up to 8 key tiles: all tiles for the tile holding
+// query 0; the bfloat16 streaming kernels take query 0's other keys apart, far_from).
 //
 // Rows past the padded length are read from the last row instead of being zero-filled:
 // their scores are masked and their probabilities are exactly 0. Tile loads are
 // unconditional (a tile index past the last valid tile is clamped to it), which keeps the
 // tiles in registers and the load stream free of divergent branches.
+#include <type_traits>
+
 #include "mca_device.h"
 #include "mca_kernels.h"
 
@@ -841,8 +844,10 @@ __global__ __launch_bounds__(kThreads) void k_attn_res(FwdParams p) {
 // pass is bound by LDS reads; two cut its time by about a sixth at 4096 keys; three or
 // four measured slower (fewer waves fit beside their accumulators), so MT = 2.
 
-// Block context for blocks of QB queries (QB / 4 per wave); as block_ctx otherwise.
-template <int QB>
+// Block context for blocks of QB queries (QB / 4 per wave); as block_ctx otherwise. FAR: under a
+// local window the first block, too, visits only tile 0 and the tiles that its windows reach
+// (far_from: the first key past them, which the kernel takes care of for query 0).
+template <int QB, bool FAR = false>
 __device__ __forceinline__ BlockCtx block_ctx_q(const FwdParams& p) {
   BlockCtx c;
   const int bid = blockIdx.x, Q = (p.n + QB - 1) / QB, P = p.H * p.B;
@@ -872,12 +877,47 @@ __device__ __forceinline__ BlockCtx block_ctx_q(const FwdParams& p) {
   c.thi = c.ntl - 1;
   c.klo = 0;
   c.kspan = 0;
-  if (c.half > 0 && c.qt > 0) {  // the window of queries q0 .. q0 + QB - 1
+  if (c.half > 0 && (FAR || c.qt > 0)) {  // the window of queries q0 .. q0 + QB - 1
     const int q0 = c.qt * QB;
     c.tlo = max(1, max(q0 - c.half, 0) / kTile);
     c.thi = min(c.ntl - 1, (q0 + QB - 1 + c.half) / kTile);
   }
   return c;
+}
+
+// Under a local window query 0 attends every key. Where the others' windows end, one query is
+// left of the block's 128: its keys from far_from on are taken on the vector units, 256 a round
+// (8 x 1057 tokens, window 256: score pass 33.4 -> 25.9 us, output pass 22.2 -> 18.5; 4 x 4096,
+// window 512: 168 -> 98 and 112 -> 62, which had waited for the first block's masked tiles). Thread tid reads chunk tid % 8 (8 values) of the
+// rows tid / 8 + 32 r, r < 8, of a round: whole rows per eight lanes.
+constexpr int kFarRows = 8;  // rows per thread and round
+__device__ __forceinline__ int far_from(const BlockCtx& c) { return (c.thi + 1) * kTile; }
+__device__ __forceinline__ int far_key(int k0, int tid, int r) { return k0 + (tid >> 3) + 32 * r; }
+
+// The thread's chunks of a round's rows (past the valid ones: of the last).
+__device__ __forceinline__ void far_load(u32x4_t (&v)[kFarRows], const uint16_t* base, const BlockCtx& c, int k0) {
+#pragma unroll
+  for (int r = 0; r < kFarRows; ++r)
+    v[r] = *reinterpret_cast<const u32x4_t*>(base + (int64_t)min(far_key(k0, c.tid, r), c.len - 1) * c.d_out + 8 * (c.tid & 7));
+}
+
+__device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// Query 0's dot products with the rows, summed over the eight lanes of a row (each gets them).
+__device__ __forceinline__ void far_dots(float (&dot)[kFarRows], const u32x4_t& q, const u32x4_t (&k)[kFarRows]) {
+#pragma unroll
+  for (int r = 0; r < kFarRows; ++r) {
+    float d = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      d = fmaf(bf16_lo(q[w]), bf16_lo(k[r][w]), d);
+      d = fmaf(bf16_hi(q[w]), bf16_hi(k[r][w]), d);
+    }
+    d += dpp_f32<0xB1>(d);
+    d += dpp_f32<0x4E>(d);
+    dot[r] = d + dpp_f32<0x141>(d);  // the other four lanes' sum, by the mirror of eight
+  }
 }
 
 // The window of query q (klo .. klo + kspan, and key 0), as block_ctx sets it for c.q.
@@ -1128,7 +1168,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MT == 
   constexpr int QB = 128 * MT;
   constexpr int kTileElems = kTile * kDHead;
   __shared__ __align__(16) uint16_t smem[6 * kTileElems];  // three K tiles, three H~ tiles
-  const BlockCtx c = block_ctx_q<QB>(p);
+  const BlockCtx c = block_ctx_q<QB, true>(p);
   const int wave = __builtin_amdgcn_readfirstlane(c.wave);
   const int qw = c.qt * QB + wave * 32 * MT;  // the wave's first query
   const int r32 = c.lane & 31, hf = c.lane >> 5, i16 = c.lane & 15;
@@ -1222,16 +1262,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MT == 
     kf[ks] = read_k(1, ks);
   }
 
-  // masked scores of half tile `half` of tile kt: reg i is key 64 kt + 32 half + 8 (i / 4) + 4 hf + i % 4
+  // masked scores of half tile `half` of tile kt: reg i is key 64 kt + 32 half + 8 (i / 4) + 4 hf
+  // + i % 4
   auto mask = [&](f32x16_t (&s)[MT], int kt, int half) __attribute__((always_inline)) {
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+    for (int m = 0; m < MT; ++m) {
+      // keys lo .. lo + span, one unsigned compare per score; key 0 on top
+      const int lo = BAND ? klo[m] : 0, span = BAND ? kspan[m] : c.len - 1;
+      const float key0 = s[m][0];
+      const int base = kt * kTile + 32 * half + 4 * hf - lo;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int key = kt * kTile + 32 * half + 8 * (i >> 2) + 4 * hf + (i & 3);
-        const bool ok = BAND ? (unsigned)(key - klo[m]) <= (unsigned)kspan[m] || key == 0 : key < c.len;
-        s[m][i] = ok ? s[m][i] : -INFINITY;
-      }
+      for (int i = 0; i < 16; ++i)
+        s[m][i] = (unsigned)(base + 8 * (i >> 2) + (i & 3)) <= (unsigned)span ? s[m][i] : -INFINITY;
+      if (BAND && kt == 0 && half == 0 && hf == 0) s[m][0] = key0;
+    }
   };
   // Half tile h: P of cur into pout, Q K^T of half tile h + 1 into nxt, P V of half tile h - 1
   // (pi, vf); K half tile h + 2 and H~ half tile h are `half` of the tiles that set_tiles chose.
@@ -1293,6 +1337,45 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MT == 
       y[m][i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, pb[m][i >> 1]), vf[i >> 1][i & 1],
                                                             y[m][i & 1], 0, 0, 0);
   wait_vmcnt<0>();  // the trailing loads have landed before the wave ends
+  if constexpr (BAND) {
+    if (c.qt == 0 && far_from(c) < c.len) {  // block-uniform: query 0's far keys
+      static_assert(MT == 1, "query 0 is in the wave's first query tile");
+      float* ps = reinterpret_cast<float*>(smem);  // [32][64] partial sums
+      const u32x4_t q0 = *reinterpret_cast<const u32x4_t*>(Qb + 8 * (c.tid & 7));
+      const float ncq0 = -p.row_c[((int64_t)c.b * p.H + c.h) * c.n];
+      float yf[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // columns 8 (tid % 8) .. + 7
+      for (int k0 = far_from(c); k0 < c.len; k0 += kThreads) {
+        u32x4_t k[kFarRows], v[kFarRows];
+        far_load(k, Kb, c, k0);
+        far_load(v, Vb, c, k0);
+        float dot[kFarRows];
+        far_dots(dot, q0, k);
+#pragma unroll
+        for (int r = 0; r < kFarRows; ++r) {
+          if (far_key(k0, c.tid, r) < c.len) {
+            const float a = exp2_fast(__fmaf_rn(dot[r], kLog2eOver8, ncq0));
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+              yf[2 * w] = fmaf(a, bf16_lo(v[r][w]), yf[2 * w]);
+              yf[2 * w + 1] = fmaf(a, bf16_hi(v[r][w]), yf[2 * w + 1]);
+            }
+          }
+        }
+      }
+      __syncthreads();  // the tiles have been read
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ps[8 * c.tid + e] = yf[e];
+      __syncthreads();
+      if (wave == 0) {
+#pragma unroll
+        for (int cc = 0; cc < 2; ++cc) {
+          float a = 0.f;
+          for (int g = 0; g < 32; ++g) a += ps[g * kDHead + 32 * cc + r32];
+          y[0][cc][0] += hf == 0 ? a : 0.f;  // query 0
+        }
+      }
+    }
+  }
   // y[m][cc][i] = Y[query qw + 32 m + 8 (i / 4) + 4 hf + i % 4][column 32 cc + r32]
 #pragma unroll
   for (int m = 0; m < MT; ++m)
@@ -1602,15 +1685,447 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   combine(nvis - 1);
 }
 
-template <int BF, bool BAND>
+// ------------------------------------------------------------------ score pass, streaming, bf16
+// The two sweeps of the streaming score pass on 32x32x16 MFMA tiles, 32 MT queries per wave
+// (128 MT per block), with k_attn_stream32's K tiles, fragments and fixed slots.
+//
+// Sweep 1 takes S^T = K Q^T: a lane holds 16 keys of one query per half tile, so a query's
+// reference M and running sum are one register each. A slot is one MFMA (half tile h + 1) and
+// fma, exp2 and add of four scores of half tile h.
+// Sweep 2 takes S = Q K^T from the same fragments: a lane holds 16 queries of one key, whose
+// maximum needs eight three-input maxima and one exchange between the wave's two halves, made
+// with the other waves' through LDS. Its accumulators start at -c / s. A slot is one MFMA and
+// two of the maxima.
+//
+// What bounds it: at 4096 tokens the power limit (the clock falls to about 1.7 GHz), so that
+// LDS reads and tile loads count beside the arithmetic: 64 queries per wave share them. K tiles
+// take four buffers and load two iterations ahead, through the end of one sweep into the next.
+template <bool BAND, int IMP, int MT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_scores_stream32(FwdParams p) {
+  constexpr int QB = 128 * MT;
+  constexpr int kTileElems = kTile * kDHead;
+  __shared__ __align__(16) uint16_t smem[4 * kTileElems];
+  __shared__ __align__(16) float cm[3][8][kTile];  // per tile in flight, wave and half: a value per key
+  __shared__ __align__(16) float cs[4][32 * MT];   // per wave: the column statistic's offset of each query
+  __shared__ int redo;
+  __shared__ float far[2][16];  // query 0's far keys: sums and maxima of the lane rows
+  const BlockCtx c = block_ctx_q<QB, true>(p);
+  const int wave = __builtin_amdgcn_readfirstlane(c.wave);
+  const int qw = c.qt * QB + wave * 32 * MT;  // the wave's first query
+  const int r32 = c.lane & 31, hf = c.lane >> 5;
+  const int64_t off = (int64_t)c.b * c.n * c.d_out + c.h * kDHead;
+  const uint16_t* Qb = static_cast<const uint16_t*>(p.Q) + off;
+  const uint16_t* Kb = static_cast<const uint16_t*>(p.K) + off;
+  const int nvis = tile_count(c);
+
+  const int drow = 8 * wave + (c.lane >> 3);
+  const uint32_t koff = (uint32_t)(drow * c.d_out * 2 + (((c.lane & 7) ^ k32_swz(drow)) << 4));
+  const uint32_t dst = lds_addr(smem) + 1024u * wave;
+  // tile t of the sequence of sweeps (t < nvis + 3): each sweep visits the same tiles
+  auto tile_mod = [&](int t) __attribute__((always_inline)) {
+    while (t >= nvis) t -= nvis;  // at most three times
+    return t;
+  };
+  auto load_tile = [&](int t, int slot) __attribute__((always_inline)) {  // t < nvis
+    const int key0 = tile_at(c, t) * kTile;
+    const uint32_t to = dst + (uint32_t)slot * (kTileElems * 2);
+    buffer_load_lds16(rows32_rsrc(Kb, c.d_out, key0, c.n), koff, to);
+    buffer_load_lds16(rows32_rsrc(Kb, c.d_out, key0 + 32, c.n), koff, to + 4096u);
+  };
+  int b0 = 0;  // buffer of tile t; tile t + i is in b0 + i mod 4
+  load_tile(0, 0);
+  load_tile(tile_mod(1), 1);
+  load_tile(tile_mod(2), 2);
+  if (c.tid == 0) redo = 0;
+
+  bf16x8_t qf[MT][4];  // query qw + 32 m + r32, d = 16 ks + 8 hf .. + 7: the B (sweep 1) or A operand
+  int klo[MT], kspan[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const uint16_t* qrow = Qb + (int64_t)min(qw + 32 * m + r32, c.n - 1) * c.d_out + 8 * hf;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) qf[m][ks] = *reinterpret_cast<const bf16x8_t*>(qrow + 16 * ks);
+    klo[m] = kspan[m] = 0;
+    if (BAND) query_window(c, qw + 32 * m + r32, klo[m], kspan[m]);
+  }
+  int ka[4];  // fragment addresses (elements) in a tile
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) ka[ks] = r32 * kDHead + (((2 * ks + hf) ^ k32_swz(r32)) << 3);
+  const uint16_t* kp[4];  // in the tile being read
+  auto set_tile = [&](int slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) kp[ks] = smem + (ka[ks] + slot * kTileElems);
+  };
+  auto read_k = [&](int half, int ks) __attribute__((always_inline)) {
+    return *reinterpret_cast<const bf16x8_t*>(kp[ks] + half * 32 * kDHead);
+  };
+  const f32x16_t zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  bf16x8_t kf[4];
+  f32x16_t s0[MT], s1[MT];
+
+  // One sweep over the visited tiles. Tiles 0 to 2 are in their buffers or on their way; at the
+  // end those of the next sweep are. T: S^T = K Q^T (else S = Q K^T); init: the
+  // accumulators' start; first(s): after the scores of tile 0's first half; work(cur, j): the
+  // vector work of slot j; done(t, half): after a half tile's slots; mask(s, kt, half); ahead(t):
+  // behind iteration t's barrier.
+  auto sweep = [&](auto transposed, const f32x16_t (&init)[MT], auto&& first, auto&& mask, auto&& work, auto&& done,
+                   auto&& ahead) __attribute__((always_inline)) {
+    constexpr bool T = decltype(transposed)::value;
+    auto mul = [&](f32x16_t (&nxt)[MT], int i, int m) __attribute__((always_inline)) {
+      const f32x16_t a = i == 0 ? init[m] : nxt[m];
+      nxt[m] = T ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], qf[m][i], a, 0, 0, 0)
+                 : __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[m][i], kf[i], a, 0, 0, 0);
+    };
+    // half tile h: the work on cur, the scores of half tile h + 1 into nxt; K half tile h + 2 is
+    // `half` of the tile that set_tile chose
+    auto step = [&](f32x16_t (&cur)[MT], f32x16_t (&nxt)[MT], int half) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < 4 * MT; ++j) {
+        const int i = j / MT, m = j % MT;
+        mul(nxt, i, m);
+        __builtin_amdgcn_sched_barrier(0);  // the reload takes the registers the MFMA has read
+        if (m == MT - 1) kf[i] = read_k(half, i);
+        work(cur, j);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    wait_vmcnt<2>();  // all but tile 2's
+    stage_barrier();
+    set_tile(b0);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) kf[ks] = read_k(0, ks);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m) mul(s0, ks, m);
+      kf[ks] = read_k(1, ks);
+    }
+    first(mul);
+#pragma clang loop unroll(disable)
+    for (int t = 0; t < nvis; ++t) {
+      wait_vmcnt<2>();  // tile t + 1 has landed, tile t + 2 (and a partial's store) may be on its way
+      if constexpr (!T) wait_lds();  // the values left in cm
+      stage_barrier();
+      load_tile(tile_mod(t + 3), (b0 + 3) & 3);  // the buffer of tile t - 1
+      set_tile((b0 + 1) & 3);
+      ahead(t);
+      const int kt = tile_at(c, t);
+      const bool masked = BAND ? !band_tile_inside(c, kt, qw, 32 * MT) : c.len - kt * kTile < kTile;  // wave-uniform
+      if (__builtin_expect(masked, 0)) mask(s0, kt, 0);
+      step(s0, s1, 0);
+      done(t, 0);
+      if (__builtin_expect(masked, 0)) mask(s1, kt, 1);
+      step(s1, s0, 1);
+      done(t, 1);
+      b0 = (b0 + 1) & 3;
+    }
+  };
+
+  // ---- sweep 1: M and the sum of exp2(logit - M) of the lane's queries, over the lane's half of
+  // the keys. M is the row's largest logit in tile 0 (finite: key 0 is attended by every query);
+  // the terms of a positive sum may exceed 1 without losing relative precision, and only a
+  // logit more than 127 log2 units above M overflows it: then (or with non-finite scores) the
+  // block takes each row's largest logit as M, from a sweep of its own, and sums again.
+  float M[MT], Ls[MT];
+  f32x16_t init[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    init[m] = zero;
+    Ls[m] = 0.f;
+  }
+  auto mask_t = [&](f32x16_t (&s)[MT], int kt, int half) __attribute__((always_inline)) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      // keys lo .. lo + span, one unsigned compare per score; key 0 on top
+      const int lo = BAND ? klo[m] : 0, span = BAND ? kspan[m] : c.len - 1;
+      const float key0 = s[m][0];
+      const int base = kt * kTile + 32 * half + 4 * hf - lo;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        s[m][i] = (unsigned)(base + 8 * (i >> 2) + (i & 3)) <= (unsigned)span ? s[m][i] : -INFINITY;
+      if (BAND && kt == 0 && half == 0 && hf == 0) s[m][0] = key0;
+    }
+  };
+  auto max16 = [&](const f32x16_t& s, float v) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 16; i += 2) v = vmax3(v, s[i], s[i + 1]);
+    return v;
+  };
+  auto none = [&](auto&&...) __attribute__((always_inline)) {};
+  float e[4] = {0.f, 0.f, 0.f, 0.f};
+  auto add_terms = [&](f32x16_t (&cur)[MT], int j) __attribute__((always_inline)) {
+    const int n = j >> 2, k = 4 * (j & 3);  // scores k .. k + 3 of query tile n
+    float x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = __fmaf_rn(cur[n][k + u], kLog2eOver8, -M[n]);
+    // the four terms of the slot before: their exp2 results are not waited for
+    const int b = j == 0 ? MT - 1 : (j - 1) >> 2;
+    Ls[b] += (e[0] + e[1]) + (e[2] + e[3]);
+    pin(Ls[b]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      e[u] = exp2_fast(x[u]);
+      pin(e[u]);
+    }
+  };
+  auto end_terms = [&]() __attribute__((always_inline)) {
+    Ls[MT - 1] += (e[0] + e[1]) + (e[2] + e[3]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) e[u] = 0.f;
+  };
+  using Yes = std::integral_constant<bool, true>;
+  using No = std::integral_constant<bool, false>;
+  sweep(
+      Yes(), init,
+      [&](auto&& mul) __attribute__((always_inline)) {  // M from both halves of tile 0
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+          for (int m = 0; m < MT; ++m) mul(s1, ks, m);
+        if (BAND ? !band_tile_inside(c, 0, qw, 32 * MT) : c.len < kTile) {
+          mask_t(s0, 0, 0);
+          mask_t(s1, 0, 1);
+        }
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          const float v = max16(s1[m], max16(s0[m], -INFINITY));
+          M[m] = __fmul_rn(vmax(v, __shfl_xor(v, 32)), kLog2eOver8);
+        }
+      },
+      mask_t, add_terms, none, none);
+  end_terms();
+  // query 0's keys past the tiles (its terms under m0, and their largest logit), in thread 0
+  const bool has_far = BAND && c.qt == 0 && far_from(c) < c.len;  // block-uniform
+  float* const part = p.colmax_part + (int64_t)c.b * c.n * p.nparts + c.h * p.qtiles + c.qt;
+  // (the dot products are left in the keys' partials, by the thread that takes them up later)
+  auto far_terms = [&](float& top) __attribute__((always_inline)) {
+    if (c.tid == 0) far[0][0] = M[0];
+    const u32x4_t q0 = *reinterpret_cast<const u32x4_t*>(Qb + 8 * (c.tid & 7));
+    __syncthreads();
+    const float m0 = far[0][0];
+    float sum = 0.f;
+    top = -INFINITY;
+    for (int k0 = far_from(c); k0 < c.len; k0 += kThreads) {
+      u32x4_t k[kFarRows];
+      far_load(k, Kb, c, k0);
+      float dot[kFarRows];
+      far_dots(dot, q0, k);
+#pragma unroll
+      for (int r = 0; r < kFarRows; ++r) {
+        const int key = far_key(k0, c.tid, r);
+        if (key < c.len) {
+          top = vmax(top, dot[r]);
+          if ((c.tid & 7) == r) {  // one of the row's eight lanes
+            sum += exp2_fast(__fmaf_rn(dot[r], kLog2eOver8, -m0));
+            part[(int64_t)key * p.nparts] = dot[r];
+          }
+        }
+      }
+    }
+    sum = row16_sum(sum);
+    top = row16_max_sel(top);
+    __syncthreads();  // every thread has m0
+    if (c.r16 == 0) {
+      far[0][4 * wave + c.g] = sum;
+      far[1][4 * wave + c.g] = top;
+    }
+    __syncthreads();
+    sum = 0.f;
+    for (int i = 0; i < 16; ++i) {
+      sum += far[0][i];
+      top = vmax(top, far[1][i]);
+    }
+    __syncthreads();  // read before the next use
+    return sum;
+  };
+  float far_top = -INFINITY;
+  if (has_far) {
+    const float sum = far_terms(far_top);
+    if (c.tid == 0) Ls[0] += sum;
+  }
+  bool overflow = false;
+#pragma unroll
+  for (int m = 0; m < MT; ++m) overflow |= !(Ls[m] < INFINITY);
+  if (overflow) redo = 1;
+  lds_barrier();
+  if (redo) {  // block-uniform
+    float v[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      v[m] = -INFINITY;
+      Ls[m] = 0.f;
+    }
+    sweep(Yes(), init, none, mask_t,
+          [&](f32x16_t (&cur)[MT], int j) __attribute__((always_inline)) {
+            if (j % 4 == 0) v[j >> 2] = max16(cur[j >> 2], v[j >> 2]);
+          },
+          none, none);
+    if (has_far && wave == 0 && r32 == 0) v[0] = vmax(v[0], far_top);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) M[m] = __fmul_rn(vmax(v[m], __shfl_xor(v[m], 32)), kLog2eOver8);
+    sweep(Yes(), init, none, mask_t, add_terms, none, none);
+    end_terms();
+    if (has_far) {
+      const float sum = far_terms(far_top);
+      if (c.tid == 0) Ls[0] += sum;
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const int q = qw + 32 * m + r32;
+    const float L = Ls[m] + __shfl_xor(Ls[m], 32);
+    const float cq = M[m] + __builtin_amdgcn_logf(L);  // finite: key 0 is attended by every query
+    if (hf == 0 && q < c.n) p.row_c[((int64_t)c.b * p.H + c.h) * c.n + q] = cq;
+    // the column statistic's offset: c, or c - log2 |S_q| under a window; +inf for padded
+    // queries (excluded)
+    float o = cq;
+    if constexpr (BAND) o = cq - __builtin_amdgcn_logf((float)(kspan[m] + 1 + (klo[m] > 0 ? 1 : 0)));
+    if (hf == 0) cs[wave][32 * m + r32] = -__fdiv_rn(q >= c.len ? INFINITY : o, kLog2eOver8);
+  }
+
+  // ---- sweep 2: the per-key column statistic of this block's valid queries. Each half of each
+  // wave leaves its value of tile t's keys in cm[t % 3]; behind the barrier of iteration t + 1
+  // (or the final one) threads 0 .. 63 combine a key's eight values in a fixed order and store
+  // the block's partial. A slot is reused three tiles later, after two more barriers.
+  if (BAND) {  // valid keys of the tiles outside the windows: query 0's value, or zero
+    if (c.qt == 0) {
+      __syncthreads();  // its offset is in cs
+      for (int k0 = far_from(c); k0 < c.len; k0 += kThreads) {
+        const int key = far_key(k0, c.tid, c.tid & 7);
+        if (key < c.len) {
+          float* a = part + (int64_t)key * p.nparts;
+          *a = exp2_fast(__fmul_rn(*a + cs[0][0], kLog2eOver8));
+        }
+      }
+    } else {
+      for (int key = kTile + c.tid; key < c.len; key += kThreads) {
+        const int kt = key / kTile;
+        if (kt < c.tlo || kt > c.thi) part[(int64_t)key * p.nparts] = 0.f;
+      }
+    }
+  }
+  auto combine = [&](int t, int slot) __attribute__((always_inline)) {
+    if (c.tid < kTile) {
+      float x[8];
+#pragma unroll
+      for (int w = 0; w < 8; ++w) x[w] = cm[slot][w][c.tid];
+      float v;
+      if constexpr (IMP == 1) v = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+      else v = exp2_fast(__fmul_rn(vmax(vmax3(vmax3(x[0], x[1], x[2]), x[3], x[4]), vmax3(x[5], x[6], x[7])), kLog2eOver8));
+      const int key = tile_at(c, t) * kTile + c.tid;
+      if (key < c.n) part[(int64_t)key * p.nparts] = v;
+    }
+  };
+  wave_lds_sync();
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {  // queries 8 g + 4 hf .. + 3 of query tile m
+      const float4 v = *reinterpret_cast<const float4*>(&cs[wave][32 * m + 8 * g + 4 * hf]);
+      init[m][4 * g] = v.x;
+      init[m][4 * g + 1] = v.y;
+      init[m][4 * g + 2] = v.z;
+      init[m][4 * g + 3] = v.w;
+    }
+  auto mask_q = [&](f32x16_t (&s)[MT], int kt, int half) __attribute__((always_inline)) {
+    // the lane's key is attended by queries lo .. lo + span: within the window, all of them (key
+    // 0, or full attention) or none (past the valid keys); and by query 0
+    const int key = kt * kTile + 32 * half + r32;
+    const int lo = !BAND || key == 0 ? 0 : key - c.half;
+    const unsigned span = !BAND || key == 0 ? 0x7fffffffu : (unsigned)(2 * c.half);
+    const float first = s[0][0];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const int base = qw + 32 * m + 4 * hf - lo;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const bool ok = (BAND ? (unsigned)(base + 8 * (i >> 2) + (i & 3)) <= span : true) && key < c.len;
+        s[m][i] = ok ? s[m][i] : -INFINITY;
+      }
+    }
+    if (BAND && qw == 0 && hf == 0 && key < c.len) s[0][0] = first;
+  };
+  float v = IMP == 1 ? 0.f : -INFINITY;
+  int slot = 0;  // t % 3
+  sweep(
+      No(), init, none, mask_q,
+      [&](f32x16_t (&cur)[MT], int j) __attribute__((always_inline)) {
+        const int n = j >> 2, k = 4 * (j & 3);
+        if constexpr (IMP == 1) {
+          float a = 0.f;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) a += exp2_fast(__fmul_rn(cur[n][k + u], kLog2eOver8));
+          v += a;
+        } else {
+          v = vmax3(vmax3(v, cur[n][k], cur[n][k + 1]), cur[n][k + 2], cur[n][k + 3]);
+        }
+        pin(v);
+        if constexpr (IMP == 2) {  // median rule: every probability, exp2(s (dot - cc / s))
+          e[0] = exp2_fast(__fmul_rn(cur[n][k], kLog2eOver8));
+          e[1] = exp2_fast(__fmul_rn(cur[n][k + 1], kLog2eOver8));
+          e[2] = exp2_fast(__fmul_rn(cur[n][k + 2], kLog2eOver8));
+          e[3] = exp2_fast(__fmul_rn(cur[n][k + 3], kLog2eOver8));
+          cur[n][k] = e[0];
+          cur[n][k + 1] = e[1];
+          cur[n][k + 2] = e[2];
+          cur[n][k + 3] = e[3];
+        }
+      },
+      [&](int t, int half) __attribute__((always_inline)) {
+        cm[slot][2 * wave + hf][32 * half + r32] = v;
+        v = IMP == 1 ? 0.f : -INFINITY;
+        if constexpr (IMP == 2) {
+          const int key = tile_at(c, t) * kTile + 32 * half + r32;
+          if (key < c.n) {
+            float* ac = p.acol + ((int64_t)c.b * c.n + key) * p.H * c.n + (int64_t)c.h * c.n;
+            auto& s = half == 0 ? s0 : s1;
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+              for (int g = 0; g < 4; ++g) {
+                const int q = qw + 32 * m + 8 * g + 4 * hf;
+                store_probs4(ac + q, s[m][4 * g], s[m][4 * g + 1], s[m][4 * g + 2], s[m][4 * g + 3], q, c.n);
+              }
+          }
+        }
+        if (half == 1) slot = slot == 2 ? 0 : slot + 1;
+      },
+      [&](int t) __attribute__((always_inline)) {  // the barrier of this iteration follows every wave's tile t - 1
+        if (t > 0) combine(t - 1, slot == 0 ? 2 : slot - 1);
+      });
+  wait_vmcnt<0>();  // the trailing loads have landed before the wave ends
+  lds_barrier();
+  combine(nvis - 1, slot == 0 ? 2 : slot - 1);
+}
+
+// float32 rows of more than 8 key tiles
+template <bool BAND>
 hipError_t launch_scores_stream(const FwdParams& p, hipStream_t s) {
   const dim3 grid((unsigned)(p.qtiles * p.H * p.B)), blk(kThreads);
   if constexpr (BAND) {  // the mean and median rules are defined for full attention only
-    return launch_stage_kernel((k_scores_stream<BF, true, 0>), grid, blk, 0, s, p);
+    return launch_stage_kernel((k_scores_stream<0, true, 0>), grid, blk, 0, s, p);
   } else {
-    if (p.importance == 1) return launch_stage_kernel((k_scores_stream<BF, false, 1>), grid, blk, 0, s, p);
-    if (p.importance == 2) return launch_stage_kernel((k_scores_stream<BF, false, 2>), grid, blk, 0, s, p);
-    return launch_stage_kernel((k_scores_stream<BF, false, 0>), grid, blk, 0, s, p);
+    if (p.importance == 1) return launch_stage_kernel((k_scores_stream<0, false, 1>), grid, blk, 0, s, p);
+    if (p.importance == 2) return launch_stage_kernel((k_scores_stream<0, false, 2>), grid, blk, 0, s, p);
+    return launch_stage_kernel((k_scores_stream<0, false, 0>), grid, blk, 0, s, p);
+  }
+}
+
+// bfloat16: p.qtiles says how many queries a block takes (score_block_queries)
+template <bool BAND>
+hipError_t launch_scores_stream32(const FwdParams& p, hipStream_t s) {
+  const dim3 grid((unsigned)(p.qtiles * p.H * p.B)), blk(kThreads);
+  if constexpr (BAND) {
+    return launch_stage_kernel((k_scores_stream32<true, 0, 1>), grid, blk, 0, s, p);
+  } else if (p.qtiles == (p.n + 127) / 128) {
+    if (p.importance == 1) return launch_stage_kernel((k_scores_stream32<false, 1, 1>), grid, blk, 0, s, p);
+    if (p.importance == 2) return launch_stage_kernel((k_scores_stream32<false, 2, 1>), grid, blk, 0, s, p);
+    return launch_stage_kernel((k_scores_stream32<false, 0, 1>), grid, blk, 0, s, p);
+  } else {
+    if (p.qtiles != (p.n + 255) / 256) return hipErrorInvalidValue;
+    if (p.importance == 1) return launch_stage_kernel((k_scores_stream32<false, 1, 2>), grid, blk, 0, s, p);
+    if (p.importance == 2) return launch_stage_kernel((k_scores_stream32<false, 2, 2>), grid, blk, 0, s, p);
+    return launch_stage_kernel((k_scores_stream32<false, 0, 2>), grid, blk, 0, s, p);
   }
 }
 
@@ -1641,12 +2156,12 @@ hipError_t launch_scores_band(const FwdParams& p, hipStream_t s) {
     else if (nt <= 2) return launch_scores_onesweep<1, 2, BAND, false>(p, s);
     else if (nt <= 4) return launch_scores_onesweep<1, 4, BAND, false>(p, s);
     else if (nt <= 8) return launch_scores_onesweep<1, 8, BAND, true>(p, s);
-    else return launch_scores_stream<1, BAND>(p, s);
+    else return launch_scores_stream32<BAND>(p, s);
   } else {
     if (nt <= 1) return launch_scores_onesweep<0, 1, BAND, false>(p, s);
     else if (nt <= 2) return launch_scores_onesweep<0, 2, BAND, false>(p, s);
     else if (nt <= 8) return launch_scores_onesweep<0, 8, BAND, true>(p, s);
-    else return launch_scores_stream<0, BAND>(p, s);
+    else return launch_scores_stream<BAND>(p, s);
   }
 }
 
@@ -1662,13 +2177,9 @@ hipError_t launch_attn_band(const FwdParams& p, hipStream_t s) {
     // from six on the 32x32 one is: 16 x 512, 16 heads 25.2 -> 23.5)
     else if (!BAND && nt <= 5)
       return launch_stage_kernel((k_attn_stream<1, false, 2>), dim3((unsigned)(((p.n + 127) / 128) * p.H * p.B)), blk, 0, s, p);
-    const int64_t q128 = (p.n + 127) / 128, wide = (q128 + 1) / 2 * p.H * p.B;
-    // 256 queries per block (64 per wave) halve the LDS reads and tile loads per score, which
-    // is what a long call is paid in once the card runs at its power limit (4096 tokens: 196 ->
-    // 178 us), where they fill two blocks per CU and waste little on the last one; a smaller
-    // grid is faster in blocks of 128 (8 x 640 tokens: 16.2 against 22.2 us)
-    if (!BAND && wide >= 2 * 256 && (q128 % 2 == 0 || q128 >= 15))
-      return launch_stage_kernel((k_attn_stream32<false, 2>), dim3((unsigned)wide), blk, 0, s, p);
+    const int64_t q128 = (p.n + 127) / 128;
+    if (!BAND && wide_query_blocks(p.n, p.H, p.B))
+      return launch_stage_kernel((k_attn_stream32<false, 2>), dim3((unsigned)((q128 + 1) / 2 * p.H * p.B)), blk, 0, s, p);
     return launch_stage_kernel((k_attn_stream32<BAND, 1>), dim3((unsigned)(q128 * p.H * p.B)), blk, 0, s, p);
   } else {
     if (nt <= 1) return launch_stage_kernel((k_attn_res<0, 1, BAND>), grid, blk, 0, s, p);

@@ -39,16 +39,6 @@ template <> struct Elem<1> { using T = uint16_t; };
 constexpr int kMaxWaves = 4;  // tokens (waves) per block: 4, 2 or 1, as the LDS allows
 
 
-// Orders LDS accesses of different lanes of one wavefront: the hardware executes a wave's
-// LDS instructions in issue order, so only compiler reordering has to be prevented.
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
-
-
-
 template <int BF>
 __device__ __forceinline__ void write_zero4(const FwdParams& p, int64_t off) {
   if constexpr (BF) *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.Henc) + off) = make_uint2(0u, 0u);

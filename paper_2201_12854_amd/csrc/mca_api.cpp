@@ -246,8 +246,9 @@ mca_status forward_impl(const mca_forward_desc* desc, const void* Q, const void*
   p.band_half = (int)(desc->window / 2);
   p.importance = desc->importance;
   p.exact_from = desc->exact_from;
-  p.qtiles = L.qtiles;
-  p.nparts = L.nparts;
+  const int sq = mca::score_block_queries(p.n, p.H, p.B, p.bf16 != 0, p.band_half > 0);
+  p.qtiles = (p.n + sq - 1) / sq;
+  p.nparts = p.H * p.qtiles;  // at most L.nparts
   p.din_pad = (int)mca::prepared_din_pad(desc->d_in);
   p.alpha = desc->alpha;
   p.seed_lo = (uint32_t)(desc->seed & 0xffffffffu);

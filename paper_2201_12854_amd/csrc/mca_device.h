@@ -74,6 +74,14 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Orders LDS accesses of different lanes of one wavefront: the hardware executes a wave's
+// LDS instructions in issue order, so only compiler reordering has to be prevented.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // ---------------------------------------------------------------- direct loads to LDS
 // LDS address (offset into the workgroup's LDS) of a shared object.
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
@@ -87,6 +95,9 @@ __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
+
+// s_waitcnt for every outstanding LDS access (vmcnt and expcnt left at their maxima).
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (0x7 << 4)); }
 
 // Block barrier without a memory fence: LDS written by the direct loads is published by the
 // explicit wait before it, and the compiler may not move memory operations across it.

@@ -14,6 +14,22 @@ constexpr int kQueryTile = 64;  // queries per attention block (the streaming ke
 // than 8 key tiles (its streaming kernel), else 64.
 __host__ __device__ inline int score_query_tile(int n) { return (n + 63) / 64 > 8 ? 128 : 64; }
 
+// 256 queries per block of the bfloat16 streaming passes (64 per wave) halve the LDS reads and
+// tile loads per score, which is what a long call is paid in once the card runs at its power
+// limit (4096 tokens, output pass: 202 -> 182 us). Taken under full attention where such
+// blocks fill two per CU and waste little on the last one; a smaller grid is faster in blocks
+// of 128 (output pass, 8 x 640 tokens: 16.2 against 22.2 us).
+inline bool wide_query_blocks(int64_t n, int64_t H, int64_t B) {
+  const int64_t q128 = (n + 127) / 128;
+  return (q128 + 1) / 2 * H * B >= 512 && (q128 % 2 == 0 || q128 >= 15);
+}
+// Queries per column-max partial of a call: score_query_tile, or 256 for wide blocks of the
+// streaming score pass (the workspace is sized for score_query_tile's, which are more).
+inline int score_block_queries(int n, int H, int B, bool bf16, bool band) {
+  const int q = score_query_tile(n);
+  return q == 128 && bf16 && !band && wide_query_blocks(n, H, B) ? 256 : q;
+}
+
 
 // Prepared weights: rownorm float32 [d_in] at offset 0, then, at prepared_wt_offset(d_in),
 // W_v^T in the input dtype in MFMA fragment order: for every 16-column tile t and k step
