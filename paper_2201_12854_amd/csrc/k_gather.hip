@@ -684,16 +684,19 @@ __global__ __launch_bounds__(kSatThreads) void k_saturated(FwdParams p) {
     }
 }
 
-// k_saturated_lds (16-byte x chunks): 16 WN NTW columns and 32 MTW tokens per block, 2 x WN
+// k_saturated_lds (16-byte x chunks): 16 WN NTW columns and 16 WM MTW tokens per block, WM x WN
 // waves of 16 MTW tokens x 16 NTW columns each, the operands staged through LDS by direct
 // global-to-LDS loads (16 bytes per lane, no registers) with ST - 1 k steps in flight. Per k
-// step the block stages its 2 MTW 16-row A tiles and WN NTW 16-column B tiles in fragment
+// step the block stages its WM MTW 16-row A tiles and WN NTW 16-column B tiles in fragment
 // order (1 KB each; lane l's 16 bytes at 16 l), and every wave reads its MTW A and NTW B
-// fragments from there. bfloat16: 128 x 256 tiles in eight waves (MTW = NTW = 4, WN = 4),
-// two per SIMD, so that one wave's LDS reads and waits pass under the other's MFMAs (eight
-// fragment reads feed 16 MFMAs); float32: 64 x 256 tiles in four waves (MTW = 2, NTW = 8,
-// WN = 2: ten fragment reads feed 16). A chunk past the end of a row re-reads the row's
-// last chunk: the prepared W_v^T is zero there.
+// fragments from there. bfloat16: 128 x 256 tiles in eight waves (MTW = NTW = 4, WM x WN =
+// 2 x 4), two per SIMD, so that one wave's LDS reads and waits pass under the other's MFMAs
+// (eight fragment reads feed 16 MFMAs). float32, whose MFMAs take 8 times as long per product:
+// 64 x 128 tiles, the four waves side by side along the columns, so that the tiles of 16
+// tokens that a block needs (one where a quarter of the tokens saturate) are shared by all its
+// SIMDs (8 x 333 tokens, d 768, 26% saturated: 53 -> 20 us against 64 x 256 tiles in 2 x 2
+// waves). A chunk past the end of a row re-reads the row's last chunk: the prepared W_v^T is
+// zero there.
 constexpr int kSatStages = 3;
 
 // One direct global-to-LDS load of 16 bytes per lane: lane l's bytes land at lds + 16 l
@@ -705,13 +708,13 @@ __device__ __forceinline__ void load_lds16(const void* g, uint32_t lds) {
   asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(lds) : "memory");
 }
 
-template <int BF, int NTW, int MTW, int ST, int WN = 2>
-__global__ __launch_bounds__(128 * WN) void k_saturated_lds(FwdParams p) {
+template <int BF, int NTW, int MTW, int ST, int WM, int WN>
+__global__ __launch_bounds__(64 * WM * WN) void k_saturated_lds(FwdParams p) {
   using T = typename Elem<BF>::T;
   constexpr int E = BF ? 8 : 4;     // elements per 16 bytes
   constexpr int KS = BF ? 32 : 16;  // k per step
-  constexpr int WV = 2 * WN;        // waves: 2 along the tokens x WN along the columns
-  constexpr int NA = 2 * MTW;       // A tiles per block (16 tokens each)
+  constexpr int WV = WM * WN;       // waves: WM along the tokens x WN along the columns
+  constexpr int NA = WM * MTW;      // A tiles per block (16 tokens each)
   constexpr int NB = WN * NTW;      // B tiles per block (16 columns each)
   constexpr int TOK = 16 * NA;      // tokens per block
   constexpr int COLS = 16 * NB;     // columns per block
@@ -761,7 +764,10 @@ __global__ __launch_bounds__(128 * WN) void k_saturated_lds(FwdParams p) {
     }
   };
   const int wm = wave / WN, wn = wave % WN;
-  const bool active = 16 * MTW * wm < nsat;  // wave-uniform
+  // the wave's 16-token tiles with a token (wave-uniform). float32: the others' MFMAs, 32 cycles
+  // each, are skipped; bfloat16: all or none
+  const int tiles = min(max((nsat - 16 * MTW * wm + 15) / 16, 0), MTW);
+  const bool active = tiles > 0;
   f32x4_t acc[MTW][NTW];
 #pragma unroll
   for (int mt = 0; mt < MTW; ++mt)
@@ -781,7 +787,8 @@ __global__ __launch_bounds__(128 * WN) void k_saturated_lds(FwdParams p) {
 #pragma unroll
       for (int nt = 0; nt < NTW; ++nt) b[nt] = st[(NA + NTW * wn + nt) * 64 + lane];
 #pragma unroll
-      for (int mt = 0; mt < MTW; ++mt)
+      for (int mt = 0; mt < MTW; ++mt) {
+        if (!BF && mt >= tiles) break;  // wave-uniform
 #pragma unroll
         for (int nt = 0; nt < NTW; ++nt) {
           if constexpr (BF) {
@@ -794,6 +801,7 @@ __global__ __launch_bounds__(128 * WN) void k_saturated_lds(FwdParams p) {
             acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[mt].w), __uint_as_float(b[nt].w), acc[mt][nt], 0, 0, 0);
           }
         }
+      }
     }
   }
   wait_vmcnt<0>();  // the trailing reloads have landed before the wave ends
@@ -863,12 +871,12 @@ hipError_t launch_saturated(const FwdParams& p, hipStream_t s) {
   const bool vec = p.d_in % (p.bf16 ? 8 : 4) == 0;
   const int64_t ntok = (int64_t)p.B * p.n;
   const dim3 grid((unsigned)(((ntok + kSatTokens - 1) / kSatTokens) * (p.d_out / kSatCols))), blk(kSatThreads);
-  if (vec && p.d_out % 256 == 0) {  // 128 (bf16) or 64 (float32) tokens x 256 columns per block
-    const int tok = p.bf16 ? 128 : 64;
-    const dim3 g2((unsigned)(((ntok + tok - 1) / tok) * (p.d_out / 256)));
-    return p.bf16 ? launch_stage_kernel(k_saturated_lds<1, 4, 4, kSatStages, 4>, g2, dim3(512), 0, s, p)
-                  : launch_stage_kernel(k_saturated_lds<0, 8, 2, kSatStages, 2>, g2, dim3(256), 0, s, p);
-  }
+  if (vec && p.bf16 && p.d_out % 256 == 0)  // 128 tokens x 256 columns per block
+    return launch_stage_kernel(k_saturated_lds<1, 4, 4, kSatStages, 2, 4>,
+                               dim3((unsigned)((ntok + 127) / 128 * (p.d_out / 256))), dim3(512), 0, s, p);
+  if (vec && !p.bf16)  // 64 tokens x 128 columns
+    return launch_stage_kernel(k_saturated_lds<0, 2, 4, kSatStages, 1, 4>,
+                               dim3((unsigned)((ntok + 63) / 64 * (p.d_out / 128))), dim3(256), 0, s, p);
   return p.bf16 ? launch_stage_kernel(k_saturated<1, false>, grid, blk, 0, s, p)
                 : launch_stage_kernel(k_saturated<0, false>, grid, blk, 0, s, p);
 }
