@@ -2184,8 +2184,13 @@ hipError_t launch_attn_band(const FwdParams& p, hipStream_t s) {
   } else {
     if (nt <= 1) return launch_stage_kernel((k_attn_res<0, 1, BAND>), grid, blk, 0, s, p);
     else if (nt <= 2) return launch_stage_kernel((k_attn_res<0, 2, BAND>), grid, blk, 0, s, p);
-    else return launch_stage_kernel((k_attn_stream<0, BAND, 2>), dim3((unsigned)(((p.n + 127) / 128) * p.H * p.B)),
-                                    blk, 0, s, p);
+    // float32, bound by its MFMAs: 128 queries per block, or 64 where whole rounds of blocks over
+    // the CUs then take less (8 x 333 tokens, 12 heads: 288 blocks, two rounds of two units,
+    // against 576, three of one: 51 -> 34 us)
+    const int64_t b128 = (int64_t)((p.n + 127) / 128) * p.H * p.B, b64 = (int64_t)nt * p.H * p.B, cus = 256;
+    if ((b64 + cus - 1) / cus < 2 * ((b128 + cus - 1) / cus))
+      return launch_stage_kernel((k_attn_stream<0, BAND, 1>), dim3((unsigned)b64), blk, 0, s, p);
+    return launch_stage_kernel((k_attn_stream<0, BAND, 2>), dim3((unsigned)b128), blk, 0, s, p);
   }
 }
 }  // namespace
