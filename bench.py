@@ -85,9 +85,9 @@ def kernel_name(stage, L):
     """The kernel a stage launches for this layer (the launch code's choice by padded length)."""
     nt = (L.seq + 63) // 64
     if stage == "scores_colmax":
-        return "k_scores_res" if nt <= (4 if L.dtype == "bf16" else 2) else "k_scores_rs" if nt <= 8 else "k_scores_stream"
+        return "k_scores_res" if nt <= (4 if L.dtype == "bf16" else 2) else "k_scores_rs" if nt <= 8 else "k_scores_stream32" if L.dtype == "bf16" else "k_scores_stream"
     if stage == "attn_out":
-        return "k_attn_res" if nt <= (4 if L.dtype == "bf16" else 2) else "k_attn_stream"
+        return "k_attn_res" if nt <= (4 if L.dtype == "bf16" else 2) else "k_attn_stream32" if L.dtype == "bf16" and (nt > 5 or L.window) else "k_attn_stream"
     return {"sample": "k_sample", "gather": "k_gather", "saturated": "k_saturated_lds"}[stage]
 
 
