@@ -24,7 +24,7 @@
 // tokens i, i + R, ...), so that padding and rows with many draws fall on all of them alike.
 // Measured against contiguous ranges, us a call: 8 x 1057 ragged, window 256: 102.2 -> 94.1;
 // 32 x 250 ragged, window 256: 79.8 -> 76.3; 64 x 128 padded: 52.7 -> 51.4; unpadded batches of
-// 32 x 128 between -0.8 and +0.7.
+// 32 x 128 between -0.7 and +0.2.
 // A block reads r and the list layout of its tokens, puts the saturated ones on one LDS list and
 // sorts the sampled tokens by the longer part of their list (key floor(8 log2), longest
 // first) with LDS atomics; its waves then take work items from an LDS counter: groups of
@@ -111,7 +111,7 @@ __device__ void saturated_group(const FwdParams& p, const int* satl, int64_t t0,
   const int d_in = p.d_in;
   const int din_pad = p.din_pad;
   // rows past the list repeat a token (their results are not stored)
-  const int64_t tk = t0 + (int64_t)satl[min(16 * gi + r16, nsat - 1)] * p.gather_bps;
+  const int64_t tk = t0 + satl[min(16 * gi + r16, nsat - 1)];
   const T* xrow = static_cast<const T*>(p.X) + (int64_t)tk * d_in;
   // B operand: W_v^T in fragment order, lane's 16 bytes of (tile c0 / 16 + c, step ks) at
   // ((tile * nks + ks) * 64 + lane) * E elements
@@ -171,7 +171,7 @@ __device__ void saturated_group(const FwdParams& p, const int* satl, int64_t t0,
   // acc[c][i] = H~[token of list row 4 g + i][c0 + 16 c + r16]; lane 4 g + i holds that token
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int64_t tok_i = t0 + (int64_t)satl[min(16 * gi + 4 * g + i, nsat - 1)] * p.gather_bps;
+    const int64_t tok_i = t0 + satl[min(16 * gi + 4 * g + i, nsat - 1)];
     if (16 * gi + 4 * g + i < nsat) {
       const int64_t base = (int64_t)tok_i * p.d_out + c0 + r16;
 #pragma unroll
@@ -191,7 +191,7 @@ __device__ void saturated_group_ldsb(const FwdParams& p, const int* satl, int64_
   const int r16 = lane & 15, g = lane >> 4;
   const int d_in = p.d_in;
   const int nks = p.din_pad / 32;
-  const int64_t tk = t0 + (int64_t)satl[min(16 * gi + r16, nsat - 1)] * p.gather_bps;
+  const int64_t tk = t0 + satl[min(16 * gi + r16, nsat - 1)];
   const uint16_t* xrow = static_cast<const uint16_t*>(p.X) + (int64_t)tk * d_in;
   constexpr int HALF = kLdsbSteps / 2;
   // the chunk offsets depend only on the lane: kept inside the item (an empty asm hides the
@@ -223,7 +223,7 @@ __device__ void saturated_group_ldsb(const FwdParams& p, const int* satl, int64_
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int64_t tok_i = t0 + (int64_t)satl[min(16 * gi + 4 * g + i, nsat - 1)] * p.gather_bps;
+    const int64_t tok_i = t0 + satl[min(16 * gi + 4 * g + i, nsat - 1)];
     if (16 * gi + 4 * g + i < nsat) {
       const int64_t base = (int64_t)tok_i * p.d_out + c0 + r16;
 #pragma unroll
@@ -321,7 +321,7 @@ __device__ void sampled_item(const FwdParams& p, const float* Ws, const uint32_t
   const int g = lane / LPR, cl = lane % LPR;
   const bool valid = s0 + g < nsampled;  // groups past the end repeat the item's first token
   const uint32_t e = order[valid ? s0 + g : s0];
-  const int64_t tk = t0 + (int64_t)(e >> kTokShift) * p.gather_bps;
+  const int64_t tk = t0 + (int64_t)__umul24(e >> kTokShift, (uint32_t)p.gather_bps);
   const int len = (int)((e >> kLenShift) & 0xfffu);
   const int nepad = (int)(e & 0x3ffu) * 2;
   const uint2* L = p.list + tk * list_stride(p.d_in);
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(kThreads) void k_gather(FwdParams p) {
   const int stride = list_stride(d_in);
 
   // the block's tokens: bis, bis + gather_bps, ...; thread tid's in the pass at t0 is
-  // t0 + tid * gather_bps
+  // t0 + tid * gather_bps (satl holds the product: the items then add it to t0 only)
   const int64_t bps = p.gather_bps, t_begin = bis, t_end = ntok;
   // the first pass's r and U, loaded together with the slice
   int r_first = 0, u_first = 0;
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(kThreads) void k_gather(FwdParams p) {
       const int len = min(uc & 0xffff, stride);                                                \
       const int nepad = min(min((uc >> 16) & 0xffff, len), 2046) & ~1;                         \
       if (exact_token(r, d_in, p.exact_from)) {                                                \
-        if (!p.sat_separate) satl[atomicAdd(ctr, 1)] = tid;                                    \
+        if (!p.sat_separate) satl[atomicAdd(ctr, 1)] = tid * p.gather_bps;                       \
       } else if (r > 0 && len > 0) {                                                           \
         key = sort_key(max(nepad, len - nepad));                                               \
         rank = atomicAdd(ctr + 2 + key, 1);                                                    \
