@@ -1141,9 +1141,9 @@ __device__ __forceinline__ int v32_swz(int row) { return ((row & 1) << 1) | ((ro
 
 // One direct load of 16 bytes per lane through the buffer descriptor rs (four scalar words)
 // at byte offset off: lane l's bytes land at lds + 16 l, zeros where the offset is out of
-// range. As load_lds16, the kernel does the waiting.
+// range. As load_lds16: the kernel does the waiting, and the s_nop is M0's wait state.
 __device__ __forceinline__ void buffer_load_lds16(u32x4_t rs, uint32_t off, uint32_t lds) {
-  asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(off), "s"(rs), "{m0}"(lds) : "memory");
+  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(off), "s"(rs), "{m0}"(lds) : "memory");
 }
 
 // Descriptor of the 32 rows from key0 on of a [*, ld] bfloat16 matrix (the head's column slice),

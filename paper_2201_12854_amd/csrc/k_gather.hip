@@ -709,9 +709,11 @@ constexpr int kSatStages = 3;
 // (lds wave-uniform, in M0: an input operand bound to that register, so the compiler sets
 // it and knows it is read). Issued through inline assembly so that the compiler does not
 // track it: the kernel waits for these loads itself (s_waitcnt vmcnt with the count of
-// loads issued after the one it needs) and publishes them with a barrier.
+// loads issued after the one it needs) and publishes them with a barrier. A scalar write of
+// M0 needs one wait state before a load to LDS; the compiler does not know the assembly as one
+// and may put the write right before it, hence the s_nop.
 __device__ __forceinline__ void load_lds16(const void* g, uint32_t lds) {
-  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(lds) : "memory");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(lds) : "memory");
 }
 
 template <int BF, int NTW, int MTW, int ST, int WM, int WN>
