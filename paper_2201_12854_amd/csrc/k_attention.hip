@@ -1523,8 +1523,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   // the lane's keys; the 16 lanes of a row are combined at the end. M is the row's largest
   // logit in tile 0 (finite: key 0 is attended by every query), and every later term is
   // added under it, with no check per tile: the terms of a positive sum may exceed 1 without
-  // losing relative precision, and only a logit more than 127 log2 units above M would
-  // overflow. If any sum came out non-finite (that, or non-finite scores), the block runs the
+  // losing relative precision, and only a sum of 2^128 or more (logits 127 log2 units above M)
+  // overflows. If any row's sum came out non-finite (that, or non-finite scores), the block runs the
   // sweep again the careful way: terms added under the current reference as long as a tile's
   // four terms of a query sum to at most 2^16, otherwise (the first tile, and rarely later)
   // the tile redone with M raised to the running max and the sum rescaled (wave-uniform).
@@ -1555,9 +1555,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
           Ls[k] += e;
         }
       });
-  bool overflow = false;
+  bool overflow = false;  // of the row's sum: lanes' parts that are finite may add up to infinity
 #pragma unroll
-  for (int k = 0; k < 8; ++k) overflow |= !(Ls[k] < INFINITY);
+  for (int k = 0; k < 8; ++k) overflow |= !(row16_sum(Ls[k]) < INFINITY);
   if (overflow) redo = 1;
   lds_barrier();  // the first sweep is done with both K buffers
   if (redo) {     // block-uniform: every wave stages its share of the tiles and meets the barriers
@@ -1823,9 +1823,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
 
   // ---- sweep 1: M and the sum of exp2(logit - M) of the lane's queries, over the lane's half of
   // the keys. M is the row's largest logit in tile 0 (finite: key 0 is attended by every query);
-  // the terms of a positive sum may exceed 1 without losing relative precision, and only a
-  // logit more than 127 log2 units above M overflows it: then (or with non-finite scores) the
-  // block takes each row's largest logit as M, from a sweep of its own, and sums again.
+  // the terms of a positive sum may exceed 1 without losing relative precision, and only a row
+  // sum of 2^128 or more (logits 127 log2 units above M) overflows: then (or with non-finite
+  // scores) the block takes each row's largest logit as M, from a sweep of its own, and sums again.
   float M[MT], Ls[MT];
   f32x16_t init[MT];
 #pragma unroll
@@ -1943,9 +1943,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
     const float sum = far_terms(far_top);
     if (c.tid == 0) Ls[0] += sum;
   }
-  bool overflow = false;
+  bool overflow = false;  // of the row's sum: two finite halves may add up to infinity
 #pragma unroll
-  for (int m = 0; m < MT; ++m) overflow |= !(Ls[m] < INFINITY);
+  for (int m = 0; m < MT; ++m) overflow |= !(Ls[m] + __shfl_xor(Ls[m], 32) < INFINITY);
   if (overflow) redo = 1;
   lds_barrier();
   if (redo) {  // block-uniform

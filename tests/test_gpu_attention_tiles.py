@@ -96,3 +96,34 @@ def test_late_logit_past_the_reference(window, dtype):
     for b, Y, Ya, m in _reference(Q, K, H, [n], heads, window):
         assert ((out.Y[b].double() - Y).abs() <= unit * Ya + 1e-30).all()
         assert ((out.colmax[b].double() - m).abs() <= (unit - 2.0 ** -8 * (dtype == "bf16") + 2e-5) * m + 2.0 ** -126).all()
+
+
+# One batch row in blocks of 128 queries, and a grid that fills two blocks per CU in blocks of 256
+# (bfloat16, full attention). The logits of 8 x 10 x 8.8125 / 8 are 127.14 log2 units: each term is
+# finite in float32 under the first tile's reference of 0, the sum of two is not. Keys 4 apart lie
+# in different halves of a wave (bfloat16) and in different lanes (float32); under the window query
+# 0 meets key 150 in its block's tiles and key 600 past them. One key of 144 units overflows alone.
+@pytest.mark.parametrize("batch,n,heads,window,keys,value", [
+    (1, 700, 4, 0, (600, 604), 8.8125), (1, 700, 4, 128, (150, 600), 8.8125), (1, 700, 4, 128, (150, 154), 8.8125),
+    (9, 1900, 8, 0, (1100, 1104), 8.8125), (9, 1900, 8, 0, (1100,), 10.0)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_late_logits_whose_sum_overflows(batch, n, heads, window, keys, value, dtype):
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    dev, d = torch.device("cuda:0"), 64 * heads
+    rng = np.random.default_rng(n + len(keys))
+    Q, K = torch.zeros(batch, n, d, device=dev), torch.zeros(batch, n, d, device=dev)
+    for h in range(heads):
+        Q[:, [0, 3, 130, n - 5], 64 * h:64 * h + 8] = 10.0
+        K[:, list(keys), 64 * h:64 * h + 8] = value
+    X = torch.from_numpy(rng.standard_normal((batch, n, d), dtype=np.float32)).to(dev)
+    W = torch.from_numpy(0.05 * rng.standard_normal((d, d), dtype=np.float32)).to(dev)
+    Q, K, X, W = (v.to(dt) for v in (Q, K, X, W))
+    r_in = torch.full((batch, n), d, dtype=torch.int32, device=dev)
+    out = mca.attention_forward(Q, K, X, W, mca.prepare_weights(W), 0.4, 1, heads=heads, r_in=r_in, window=window,
+                                export=True)
+    H = out.encoded.to(dt).double()
+    # the rounding of a float32 logit of 144 log2 units, times ln 2, beside the probabilities'
+    logit, unit = 4 * 0.6931 * 2.0 ** -24 * 145, 2.0 ** -8 if dtype == "bf16" else 1e-5
+    for b, Y, Ya, m in _reference(Q, K, H, [n] * batch, heads, window):
+        assert ((out.Y[b].double() - Y).abs() <= (logit + unit) * Ya + 1e-30).all(), b
+        assert ((out.colmax[b].double() - m).abs() <= (logit + 2e-5) * m + 2.0 ** -126).all(), b
