@@ -1159,6 +1159,13 @@ __device__ __forceinline__ u32x4_t rows32_rsrc(const void* base, int ld, int key
   return w;
 }
 
+// s += b with the rounding error of the sum added to c (Knuth's two-sum).
+__device__ __forceinline__ void add_carry(float& s, float& c, float b) {
+  const float t = s + b, z = t - s;
+  c += (s - (t - z)) + (b - z);
+  s = t;
+}
+
 // Keeps the computation of x before this point and what follows behind it.
 template <typename T>
 __device__ __forceinline__ void pin(T& x) { asm volatile("" : "+v"(x)); }
@@ -1765,8 +1772,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
 
   // One sweep over the visited tiles. Tiles 0 to 2 are in their buffers or on their way; at the
   // end those of the next sweep are. T: S^T = K Q^T (else S = Q K^T); init: the
-  // accumulators' start; first(s): after the scores of tile 0's first half; work(cur, j): the
-  // vector work of slot j; done(t, half): after a half tile's slots; mask(s, kt, half); ahead(t):
+  // accumulators' start; first(s): after the scores of tile 0's first half; work(cur, j, half):
+  // the vector work of slot j; done(t, half): after a half tile's slots; mask(s, kt, half); ahead(t):
   // behind iteration t's barrier.
   auto sweep = [&](auto transposed, const f32x16_t (&init)[MT], auto&& first, auto&& mask, auto&& work, auto&& done,
                    auto&& ahead) __attribute__((always_inline)) {
@@ -1785,7 +1792,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
         mul(nxt, i, m);
         __builtin_amdgcn_sched_barrier(0);  // the reload takes the registers the MFMA has read
         if (m == MT - 1) kf[i] = read_k(half, i);
-        work(cur, j);
+        work(cur, j, half);
         __builtin_amdgcn_sched_barrier(0);
       }
     };
@@ -1826,12 +1833,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
   // the terms of a positive sum may exceed 1 without losing relative precision, and only a row
   // sum of 2^128 or more (logits 127 log2 units above M) overflows: then (or with non-finite
   // scores) the block takes each row's largest logit as M, from a sweep of its own, and sums again.
-  float M[MT], Ls[MT];
+  //
+  // A lane adds half of a row, so the sum is taken in levels, lest the rounding of n / 8 additions
+  // into one register be left in it: the terms of a tile in Lt, four tiles in Lu, and those in
+  // Ls + Lc, the rounding errors of Ls kept in Lc (add_carry). Root mean square of the sum's
+  // relative error in float32, normal logits (emulated; the 16x16 kernel's order in brackets):
+  // 3.7e-8 (4.7e-8) at 576 keys, 3.4e-8 (5.8e-8) at 4096, 3.3e-8 (7.4e-8) at 16384; one register
+  // 1.0e-7, 2.3e-7, 4.5e-7.
+  float M[MT], Ls[MT], Lc[MT], Lu[MT], Lt[MT];
   f32x16_t init[MT];
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
     init[m] = zero;
-    Ls[m] = 0.f;
+    Ls[m] = Lc[m] = Lu[m] = Lt[m] = 0.f;
   }
   auto mask_t = [&](f32x16_t (&s)[MT], int kt, int half) __attribute__((always_inline)) {
 #pragma unroll
@@ -1853,25 +1867,47 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
   };
   auto none = [&](auto&&...) __attribute__((always_inline)) {};
   float e[4] = {0.f, 0.f, 0.f, 0.f};
-  auto add_terms = [&](f32x16_t (&cur)[MT], int j) __attribute__((always_inline)) {
+  auto add_terms = [&](f32x16_t (&cur)[MT], int j, int half) __attribute__((always_inline)) {
     const int n = j >> 2, k = 4 * (j & 3);  // scores k .. k + 3 of query tile n
     float x[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) x[u] = __fmaf_rn(cur[n][k + u], kLog2eOver8, -M[n]);
     // the four terms of the slot before: their exp2 results are not waited for
     const int b = j == 0 ? MT - 1 : (j - 1) >> 2;
-    Ls[b] += (e[0] + e[1]) + (e[2] + e[3]);
-    pin(Ls[b]);
+    const float sum = (e[0] + e[1]) + (e[2] + e[3]);
+    // the first since Lt went into Lu (for the last query tile those of the tile before)
+    if (half == 0 && (b == MT - 1 ? j == 0 : j == 4 * b + 1)) Lt[b] = sum;
+    else Lt[b] += sum;
+    pin(Lt[b]);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       e[u] = exp2_fast(x[u]);
       pin(e[u]);
     }
   };
+  auto end_tile = [&](int t, int half) __attribute__((always_inline)) {
+    if (half == 0) return;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) Lu[m] += Lt[m];
+    if ((t & 3) == 3) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        add_carry(Ls[m], Lc[m], Lu[m]);
+        Lu[m] = 0.f;
+      }
+    }
+  };
   auto end_terms = [&]() __attribute__((always_inline)) {
-    Ls[MT - 1] += (e[0] + e[1]) + (e[2] + e[3]);
+    Lu[MT - 1] += (e[0] + e[1]) + (e[2] + e[3]);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) add_carry(Ls[m], Lc[m], Lu[m]);
 #pragma unroll
     for (int u = 0; u < 4; ++u) e[u] = 0.f;
+  };
+  auto row_sum = [&](int m) __attribute__((always_inline)) {  // both halves of the wave
+    float L = Ls[m], carry = Lc[m] + __shfl_xor(Lc[m], 32);
+    add_carry(L, carry, __shfl_xor(Ls[m], 32));
+    return L + carry;
   };
   using Yes = std::integral_constant<bool, true>;
   using No = std::integral_constant<bool, false>;
@@ -1892,7 +1928,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
           M[m] = __fmul_rn(vmax(v, __shfl_xor(v, 32)), kLog2eOver8);
         }
       },
-      mask_t, add_terms, none, none);
+      mask_t, add_terms, end_tile, none);
   end_terms();
   // query 0's keys past the tiles (its terms under m0, and their largest logit), in thread 0
   const bool has_far = BAND && c.qt == 0 && far_from(c) < c.len;  // block-uniform
@@ -1930,22 +1966,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
       far[1][4 * wave + c.g] = top;
     }
     __syncthreads();
-    sum = 0.f;
-    for (int i = 0; i < 16; ++i) {
-      sum += far[0][i];
-      top = vmax(top, far[1][i]);
-    }
+    sum = row16_sum(far[0][c.r16]);
+    top = row16_max_sel(far[1][c.r16]);
     __syncthreads();  // read before the next use
     return sum;
   };
   float far_top = -INFINITY;
   if (has_far) {
     const float sum = far_terms(far_top);
-    if (c.tid == 0) Ls[0] += sum;
+    if (c.tid == 0) add_carry(Ls[0], Lc[0], sum);
   }
   bool overflow = false;  // of the row's sum: two finite halves may add up to infinity
 #pragma unroll
-  for (int m = 0; m < MT; ++m) overflow |= !(Ls[m] + __shfl_xor(Ls[m], 32) < INFINITY);
+  for (int m = 0; m < MT; ++m) overflow |= !(row_sum(m) < INFINITY);
   if (overflow) redo = 1;
   lds_barrier();
   if (redo) {  // block-uniform
@@ -1953,28 +1986,27 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
       v[m] = -INFINITY;
-      Ls[m] = 0.f;
+      Ls[m] = Lc[m] = Lu[m] = Lt[m] = 0.f;
     }
     sweep(Yes(), init, none, mask_t,
-          [&](f32x16_t (&cur)[MT], int j) __attribute__((always_inline)) {
+          [&](f32x16_t (&cur)[MT], int j, int) __attribute__((always_inline)) {
             if (j % 4 == 0) v[j >> 2] = max16(cur[j >> 2], v[j >> 2]);
           },
           none, none);
     if (has_far && wave == 0 && r32 == 0) v[0] = vmax(v[0], far_top);
 #pragma unroll
     for (int m = 0; m < MT; ++m) M[m] = __fmul_rn(vmax(v[m], __shfl_xor(v[m], 32)), kLog2eOver8);
-    sweep(Yes(), init, none, mask_t, add_terms, none, none);
+    sweep(Yes(), init, none, mask_t, add_terms, end_tile, none);
     end_terms();
     if (has_far) {
       const float sum = far_terms(far_top);
-      if (c.tid == 0) Ls[0] += sum;
+      if (c.tid == 0) add_carry(Ls[0], Lc[0], sum);
     }
   }
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
     const int q = qw + 32 * m + r32;
-    const float L = Ls[m] + __shfl_xor(Ls[m], 32);
-    const float cq = M[m] + __builtin_amdgcn_logf(L);  // finite: key 0 is attended by every query
+    const float cq = M[m] + __builtin_amdgcn_logf(row_sum(m));  // finite: key 0 is attended by every query
     if (hf == 0 && q < c.n) p.row_c[((int64_t)c.b * p.H + c.h) * c.n + q] = cq;
     // the column statistic's offset: c, or c - log2 |S_q| under a window; +inf for padded
     // queries (excluded)
@@ -2049,7 +2081,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
   int slot = 0;  // t % 3
   sweep(
       No(), init, none, mask_q,
-      [&](f32x16_t (&cur)[MT], int j) __attribute__((always_inline)) {
+      [&](f32x16_t (&cur)[MT], int j, int) __attribute__((always_inline)) {
         const int n = j >> 2, k = 4 * (j & 3);
         if constexpr (IMP == 1) {
           float a = 0.f;

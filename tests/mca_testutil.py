@@ -38,10 +38,14 @@ TOL_H = 1e-5
 #      quadratic form is at most ln2 |dz|_max^2, so perturbations dz_k of the logits move
 #      c by at most sum_k p_k |dz_k| + (ln2 / 2) max_k dz_k^2; the sum L of exp2 terms has
 #      relative error <= (u/2) ln2 R (rounding of each fma argument; R the row's logit
-#      range) + eps_exp (each exp2) + gamma_{n/16 + 6} (a lane adds its keys in sequence,
-#      then four butterfly levels combine 16 lanes), plus, in the streaming kernel, one
-#      rescale per visited key tile at most (eps_exp + u each, arguments summing to at
-#      most R) and four DPP combination levels; log2 L within 2u max(1, log2 L), where L is
+#      range) + eps_exp (each exp2) + gamma of the additions in sequence: n/16 + 6 (a lane adds
+#      its keys, then four butterfly levels combine 16 lanes), or, in the bfloat16 streaming
+#      kernel, 16 (2 for four terms, 7 for a tile, 4 for four tiles, whose sums are added
+#      with their rounding errors kept aside, then both halves of the wave), and under a
+#      window n/256 + 8 for query 0's far keys and 1 for their sum; plus, in the float32
+#      streaming kernel, one rescale per visited key tile at most (eps_exp + u each,
+#      arguments summing to at most R) and four DPP combination levels; log2 L within
+#      2u max(1, log2 L), where L is
 #      the sum under the kernel's reference M (the row's largest logit in its first key
 #      tile, or a larger logit of the row once raised), so log2 L is at most the oracle's
 #      log2 of the sum under the row max plus (row max - largest logit of tile 0); the
@@ -49,9 +53,9 @@ TOL_H = 1e-5
 #   t: the fma rounds by |t| u / 2
 #   m: exp2 of the maximum: eps_exp; the maximum of perturbed values moves by at most
 #      the largest perturbation among the pairs that can be the maximum
-# The streaming kernel (rows longer than 8 key tiles) differs in three places: its running
-# reference sits up to 16 log2 units below the row max (the exp2 arguments reach R + 16);
-# its column statistic starts the MFMA accumulator at d = float32(c~ / s32) and takes
+# The streaming kernels (rows longer than 8 key tiles) differ in two places: the float32
+# one's running reference sits up to 16 log2 units below the row max (the exp2 arguments
+# reach R + 16); their column statistic starts the MFMA accumulator at d = float32(c~ / s32) and takes
 # t~ = s32 max(dot - d): the rounding of d (|c| u / 2) and the accumulation of 64 products
 # onto it (gamma_65 |c|, as the products' own term) add to the error of t.
 # eps_exp = 2 ulp: v_exp_f32 and v_log_f32 are specified to 1 ulp; a factor of two is kept
@@ -97,8 +101,10 @@ def colmax_tolerance(L, importance="max", window=None):
             c = zmax + np.log2(Ls)
             R = zmax - np.where(att, z, np.inf).min(axis=1)
             lgL = np.log2(Ls) + (zmax - z[:, :64].max(axis=1))  # log2 of the sum under tile 0's max
-            dL = ln2 * (U32 / 2) * (R + (16.0 if streaming else 0.0)) + EPS_EXP + _gamma(-(-n // 16) + 6)
-            if streaming:
+            raised = streaming and L.dtype == "f32"  # a running reference, rescaled as it is raised
+            adds = -(-n // 16) + 6 if raised or not streaming else 16 + (-(-n // 256) + 9 if window > 0 else 0)
+            dL = ln2 * (U32 / 2) * (R + (16.0 if raised else 0.0)) + EPS_EXP + _gamma(adds)
+            if raised:
                 dL = dL + ntiles * (EPS_EXP + U32) + ln2 * (U32 / 2) * R + 4 * (EPS_EXP + 1.5 * U32) \
                      + ln2 * (U32 / 2) * R
             dz = np.where(att, S32 * e + ds * np.abs(dot), 0.0)  # logit perturbations

@@ -127,3 +127,25 @@ def test_late_logits_whose_sum_overflows(batch, n, heads, window, keys, value, d
     for b, Y, Ya, m in _reference(Q, K, H, [n] * batch, heads, window):
         assert ((out.Y[b].double() - Y).abs() <= (logit + unit) * Ya + 1e-30).all(), b
         assert ((out.colmax[b].double() - m).abs() <= (logit + 2e-5) * m + 2.0 ** -126).all(), b
+
+
+# Row sums of equal terms: adding the same term to a growing float32 sum rounds the same way every
+# time, so a long chain of additions shows (16384 keys: 2e-5 for n / 8 additions in one register).
+# Every query has key 0's logit 0 and the others' -a / 8; blocks of 128 queries, then of 256.
+@pytest.mark.parametrize("a", [1.0, 1.5, 2.25, 3.625, 4.25, 5.5])
+@pytest.mark.parametrize("batch", [1, 2])
+def test_long_row_sums(batch, a):
+    n, heads, dev = 16384, 4, torch.device("cuda:0")
+    Q, K = (torch.zeros(batch, n, 64 * heads, dtype=torch.bfloat16, device=dev) for _ in range(2))
+    Q[:, :, ::64], K[:, 1:, ::64] = a, -1.0
+    X, W = torch.ones(batch, n, 8, dtype=torch.bfloat16, device=dev), torch.ones(8, 64 * heads, dtype=torch.bfloat16, device=dev)
+    out = mca.attention_forward(Q, K, X, W, mca.prepare_weights(W), 0.4, 1, heads=heads, export=True,
+                                r_in=torch.zeros(batch, n, dtype=torch.int32, device=dev))
+    x = np.exp(-a / 8)
+    m = torch.full((n,), x, dtype=torch.float64, device=dev)
+    m[0] = 1.0
+    m /= 1 + (n - 1) * x
+    # In units u = 2^-24: the sum's 15 roundings in sequence, each exp2 to two ulps (twice 4), and the
+    # exponent, up to 14: log2 to two ulps (4 x 14), its division by the scale, the addition to the
+    # dot product and the product with the scale (3 x 14), times ln 2; the exponents of the terms.
+    assert ((out.colmax.double() - m).abs() <= (15 + 8 + 0.6932 * 7 * 14 + 2) * 2.0 ** -24 * m).all()
