@@ -12,11 +12,13 @@ if torch.cuda.is_available():
 
 # (batch, n, heads, window, ragged): the resident kernels' last lengths, the 16x16 output pass
 # (5 key tiles), then 32x32 tiles with partial query and key tiles in blocks of 128 queries, and
-# grids that fill two blocks per CU in blocks of 256 (whole, and with a short last block)
+# grids that fill two blocks per CU in blocks of 256 (whole, and with a short last block). float32:
+# the output pass in blocks of 64 queries (most), and of 128 where these take no more rounds over
+# the CUs (64 x 500; 8 x 512, 8 heads under a window)
 SHAPES = [(2, 64, 4, 0, True), (2, 256, 4, 0, True), (2, 257, 4, 0, True), (1, 320, 4, 0, False),
           (2, 321, 4, 0, True), (1, 384, 8, 0, False), (2, 449, 4, 0, True), (1, 513, 4, 0, False),
           (2, 577, 4, 0, True), (2, 300, 4, 64, True), (2, 333, 4, 2, True), (1, 1057, 4, 256, False),
-          (64, 500, 8, 0, True), (9, 1900, 8, 0, True)]
+          (64, 500, 8, 0, True), (9, 1900, 8, 0, True), (8, 512, 8, 64, True)]
 
 
 def _reference(Q, K, H, lens, heads, window):
@@ -46,8 +48,6 @@ def _reference(Q, K, H, lens, heads, window):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("batch,n,heads,window,ragged", SHAPES)
 def test_attention_passes(batch, n, heads, window, ragged, dtype):
-    if dtype == "f32" and batch * n > 4096:
-        pytest.skip("the float32 passes have no variant for large grids")
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     dev, d = torch.device("cuda:0"), 64 * heads
     rng = np.random.default_rng(1000 * n + heads + window)
@@ -68,6 +68,29 @@ def test_attention_passes(batch, n, heads, window, ragged, dtype):
         assert (err <= unit * Ya + 1e-30).all(), (b, (err / Ya).max().item())
         L = int(lens[b])
         assert ((out.colmax[b, :L].double() - m[:L]).abs() <= 2e-5 * m[:L] + 2.0 ** -126).all(), b
+        assert (out.colmax[b, L:] == 0).all()
+
+
+# The mean and median rules where the bfloat16 score pass takes blocks of 256 queries, and of 128.
+@pytest.mark.parametrize("batch,n,heads", [(9, 1900, 8), (2, 700, 4)])
+@pytest.mark.parametrize("importance", ["mean", "median"])
+def test_rules_of_the_streaming_score_pass(batch, n, heads, importance):
+    dev, d = torch.device("cuda:0"), 64 * heads
+    rng = np.random.default_rng(n)
+    new = lambda *s: torch.from_numpy(rng.standard_normal(s, dtype=np.float32)).to(dev).bfloat16()  # noqa: E731
+    Q, K, X, W = 2 * new(batch, n, d), 0.5 * new(batch, n, d), new(batch, n, 8), new(8, d)
+    lens = rng.integers(n // 2, n + 1, batch)
+    out = mca.attention_forward(Q, K, X, W, mca.prepare_weights(W), 0.4, 1, heads=heads, export=True, importance=importance,
+                                r_in=torch.zeros(batch, n, dtype=torch.int32, device=dev),
+                                seq_lens=torch.from_numpy(lens.astype(np.int32)).to(dev))
+    for b in range(batch):
+        L = int(lens[b])
+        A = torch.cat([torch.softmax(Q[b, :L, c:c + 64].double() @ K[b, :L, c:c + 64].double().t() / 8, 1)
+                       for c in range(0, d, 64)])
+        m = A.mean(0) if importance == "mean" else A.sort(0).values[[(len(A) - 1) // 2, len(A) // 2]].mean(0)
+        # each probability as in test_attention_passes; their sum in a chain of at most 100 additions
+        # (32 x MT queries of a half wave, the eight halves, heads x query blocks)
+        assert ((out.colmax[b, :L].double() - m).abs() <= (2e-5 + 100 * 2.0 ** -24) * m).all(), b
         assert (out.colmax[b, L:] == 0).all()
 
 
