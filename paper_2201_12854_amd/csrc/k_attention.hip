@@ -25,8 +25,9 @@
 //     kept in registers, still a single pass;
 //   streaming (longer sequences): tiles are double buffered in LDS with the next tile
 //     prefetched into registers; the score pass sweeps twice (per-lane statistics, then
-//     the column statistic). The bf16 output pass of six key tiles or more uses 32x32x16
-//     MFMA tiles and direct loads to LDS (k_attn_stream32).
+//     the column statistic). The bf16 kernels use 32x32x16 MFMA tiles and direct loads to
+//     LDS (k_scores_stream32, k_attn_stream32; large grids of 5 to 8 key tiles keep the
+//     16x16 output pass).
 // Local-window attention (Sec. "Longformer": a window of w keys around each token and a
 // global first token): query q attends key k < len when |q - k| <= w / 2, or q = 0, or
 // k = 0; the other scores are masked like padded keys. The column max is then taken of
@@ -2205,22 +2206,26 @@ hipError_t launch_attn_band(const FwdParams& p, hipStream_t s) {
     if (nt <= 1) return launch_stage_kernel((k_attn_res<1, 1, BAND>), grid, blk, 0, s, p);
     else if (nt <= 2) return launch_stage_kernel((k_attn_res<1, 2, BAND>), grid, blk, 0, s, p);
     else if (nt <= 4) return launch_stage_kernel((k_attn_res<1, 4, BAND>), grid, blk, 0, s, p);
-    // five key tiles: the 16x16 kernel is the faster one (16 x 300 tokens: 13.2 against 14.2 us;
-    // from six on the 32x32 one is: 16 x 512, 16 heads 25.2 -> 23.5)
-    else if (!BAND && nt <= 5)
-      return launch_stage_kernel((k_attn_stream<1, false, 2>), dim3((unsigned)(((p.n + 127) / 128) * p.H * p.B)), blk, 0, s, p);
     const int64_t q128 = (p.n + 127) / 128;
-    if (!BAND && wide_query_blocks(p.n, p.H, p.B))
+    if (!BAND && wide_output_blocks(p.n, p.H, p.B))
       return launch_stage_kernel((k_attn_stream32<false, 2>), dim3((unsigned)((q128 + 1) / 2 * p.H * p.B)), blk, 0, s, p);
+    // Rows of up to 8 key tiles: the 16x16 kernel where a CU gets five blocks or more (the cause was
+    // not isolated; 96 x 448, 4 heads: 28.4 against 29.8 us; 256 x 300: 41.2 against 44.6), below
+    // that the 32x32 one, whose blocks take less time each (6 x 512, 4 heads 9.2 against 8.1; 16 x
+    // 384, 16 heads 15.8 against 15.2).
+    if (!BAND && nt <= 8 && blocks_per_cu(q128 * p.H * p.B) >= 5)
+      return launch_stage_kernel((k_attn_stream<1, false, 2>), dim3((unsigned)(q128 * p.H * p.B)), blk, 0, s, p);
     return launch_stage_kernel((k_attn_stream32<BAND, 1>), dim3((unsigned)(q128 * p.H * p.B)), blk, 0, s, p);
   } else {
     if (nt <= 1) return launch_stage_kernel((k_attn_res<0, 1, BAND>), grid, blk, 0, s, p);
     else if (nt <= 2) return launch_stage_kernel((k_attn_res<0, 2, BAND>), grid, blk, 0, s, p);
-    // float32, bound by its MFMAs: 128 queries per block, or 64 where whole rounds of blocks over
-    // the CUs then take less (8 x 333 tokens, 12 heads: 288 blocks, two rounds of two units,
-    // against 576, three of one: 51 -> 34 us)
-    const int64_t b128 = (int64_t)((p.n + 127) / 128) * p.H * p.B, b64 = (int64_t)nt * p.H * p.B, cus = 256;
-    if ((b64 + cus - 1) / cus < 2 * ((b128 + cus - 1) / cus))
+    // float32, bound by its MFMAs: 128 queries per block, or 64 (half the work each) where the CU
+    // with the most blocks then has less (8 x 333 tokens, 12 heads: two blocks per CU against three
+    // of half the work, 51 -> 34 us). Blocks of 64, us a call against those of 128, 12 heads: 1 x 200 41.0
+    // (50.0), 2 x 640 106.9 (126.2), 4 x 1024 291.6 (314.3), window 256 267.0 (326.0); where the
+    // rule keeps 128: 32 x 200 142.2 (140.4), 4 x 512, 16 heads 95.5 (98.5).
+    const int64_t b128 = (int64_t)((p.n + 127) / 128) * p.H * p.B, b64 = (int64_t)nt * p.H * p.B;
+    if (blocks_per_cu(b64) < 2 * blocks_per_cu(b128))
       return launch_stage_kernel((k_attn_stream<0, BAND, 1>), dim3((unsigned)b64), blk, 0, s, p);
     return launch_stage_kernel((k_attn_stream<0, BAND, 2>), dim3((unsigned)b128), blk, 0, s, p);
   }

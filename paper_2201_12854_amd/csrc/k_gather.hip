@@ -829,20 +829,8 @@ __global__ __launch_bounds__(64 * WM * WN) void k_saturated_lds(FwdParams p) {
     }
 }
 
-// Per-device host caches below are atomics: concurrent host threads may fill them at once
+// The per-device host caches are atomics: concurrent host threads may fill them at once
 // (each writes the same value), and a reader sees either 0 (not yet known) or that value.
-int device_cus() {
-  static std::atomic<int> cached[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  int n = cached[dev].load(std::memory_order_acquire);
-  if (!n) {
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-    cached[dev].store(n, std::memory_order_release);
-  }
-  return n;
-}
-
 template <int BF, int WC, bool VEC, bool LDSB>
 hipError_t launch_wc(const FwdParams& p, hipStream_t s) {
   const size_t lds = gather_lds_bytes(p.d_in, WC, LDSB);
@@ -867,6 +855,19 @@ hipError_t launch_wc(const FwdParams& p, hipStream_t s) {
 }
 
 }  // namespace
+
+// Cached per device, as in launch_wc.
+int device_cus() {
+  static std::atomic<int> cached[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  int n = cached[dev].load(std::memory_order_acquire);
+  if (!n) {
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+    cached[dev].store(n, std::memory_order_release);
+  }
+  return n;
+}
 
 // Blocks per slice: every block gets a CU of its own (a block holds most of a CU's LDS).
 int gather_blocks_per_slice(int d_in, int d_out) {

@@ -14,22 +14,47 @@ constexpr int kQueryTile = 64;  // queries per attention block (the streaming ke
 // than 8 key tiles (its streaming kernel), else 64.
 __host__ __device__ inline int score_query_tile(int n) { return (n + 63) / 64 > 8 ? 128 : 64; }
 
+// CUs of the current device (256 if it cannot be asked).
+int device_cus();
+// The most blocks that one CU gets, which is what a grid of equal blocks takes.
+inline int64_t blocks_per_cu(int64_t blocks) { return (blocks + device_cus() - 1) / device_cus(); }
+
 // 256 queries per block of the bfloat16 streaming passes (64 per wave) halve the LDS reads and
-// tile loads per score, which is what a long call is paid in once the card runs at its power
-// limit (4096 tokens, output pass: 202 -> 182 us). Taken under full attention where such
-// blocks fill two per CU and waste little on the last one; a smaller grid is faster in blocks
-// of 128 (output pass, 8 x 640 tokens: 16.2 against 22.2 us).
+// tile loads per score. Taken under full attention where such blocks fill two per CU and waste
+// little on the last one (a smaller grid is faster in blocks of 128: output pass, 8 x 640
+// tokens 16.2 against 22.2 us), and where the fewer blocks save more than the last round of them
+// costs. Measured over 400 to 3072 tokens and grids of 350 to 1400 blocks, a block of 256 takes as
+// long as 1.55 to 1.7 blocks of 128 in the score pass and 1.7 to 1.8 in the output pass (n <= 512:
+// 1.85). Output pass, 128 against 256 queries per block: 16 x 2048, 4 heads (4 blocks per CU
+// against 2) 71.3 and 63.9 us; 18 x 2048 (5 against 3) 83.1 and 86.8; 25 x 1920 (6 against 4) 95.7
+// and 107; 66 x 512 (5 against 3) 27.5 and 29.7. Score pass: 17 x 1920 (4 against 3) 78.7 and 89.9;
+// 18 x 2048 102 and 99.
 inline bool wide_query_blocks(int64_t n, int64_t H, int64_t B) {
   const int64_t q128 = (n + 127) / 128;
-  return (q128 + 1) / 2 * H * B >= 512 && (q128 % 2 == 0 || q128 >= 15);
+  return (q128 + 1) / 2 * H * B >= 2 * device_cus() && (q128 % 2 == 0 || q128 >= 15);
+}
+inline bool wide_score_blocks(int64_t n, int64_t H, int64_t B) {
+  const int64_t q128 = (n + 127) / 128;
+  return wide_query_blocks(n, H, B) &&
+         3 * blocks_per_cu(q128 * H * B) >= 5 * blocks_per_cu((q128 + 1) / 2 * H * B);
+}
+// In the output pass also where the blocks of a (batch row, head) cannot be kept on one XCD (H B
+// not a multiple of 8) and rows of up to 1024 tokens put many of them in flight at once: every
+// XCD's L2 then loads the tiles of nearly all, half as often from blocks of 256 (65 x 512, 4 heads:
+// 31.9 against 29.6 us; 41 x 1024: 65.1 against 49.8; 23 x 1536 is past it, 64.0 against 67.9).
+inline bool wide_output_blocks(int64_t n, int64_t H, int64_t B) {
+  const int64_t q128 = (n + 127) / 128;
+  if (!wide_query_blocks(n, H, B)) return false;
+  if (H * B % 8 != 0 && n <= 1024) return true;
+  const int64_t c128 = blocks_per_cu(q128 * H * B), c256 = blocks_per_cu((q128 + 1) / 2 * H * B);
+  return n <= 512 ? c128 >= 2 * c256 : 4 * c128 >= 7 * c256;
 }
 // Queries per column-max partial of a call: score_query_tile, or 256 for wide blocks of the
 // streaming score pass (the workspace is sized for score_query_tile's, which are more).
 inline int score_block_queries(int n, int H, int B, bool bf16, bool band) {
   const int q = score_query_tile(n);
-  return q == 128 && bf16 && !band && wide_query_blocks(n, H, B) ? 256 : q;
+  return q == 128 && bf16 && !band && wide_score_blocks(n, H, B) ? 256 : q;
 }
-
 
 // Prepared weights: rownorm float32 [d_in] at offset 0, then, at prepared_wt_offset(d_in),
 // W_v^T in the input dtype in MFMA fragment order: for every 16-column tile t and k step
@@ -61,7 +86,7 @@ struct FwdParams {
                         // first token attends and is attended by all (0: full attention)
   int importance;       // per-key statistic of the count rule: 0 max, 1 mean, 2 median
   int exact_from;       // > 0: tokens with r >= exact_from are encoded exactly too
-  int qtiles;   // query tiles per sequence = ceil(n / score_query_tile(n))
+  int qtiles;   // score pass blocks per (sequence, head) = ceil(n / score_block_queries)
   int nparts;   // column-max partials per token = H * qtiles
   int din_pad;  // row length of W_v^T
   double alpha;

@@ -10,15 +10,18 @@ pytestmark = pytest.mark.gpu
 if torch.cuda.is_available():
     import paper_2201_12854_amd as mca
 
-# (batch, n, heads, window, ragged): the resident kernels' last lengths, the 16x16 output pass
-# (5 key tiles), then 32x32 tiles with partial query and key tiles in blocks of 128 queries, and
-# grids that fill two blocks per CU in blocks of 256 (whole, and with a short last block). float32:
-# the output pass in blocks of 64 queries (most), and of 128 where these take no more rounds over
-# the CUs (64 x 500; 8 x 512, 8 heads under a window)
+# (batch, n, heads, window, ragged): the resident kernels' last lengths; the 32x32 output pass with
+# partial query and key tiles in blocks of 128 queries, and of 256 where these fill two blocks per
+# CU (64 x 500; 8 x 1900 with a short last block; 43 x 500, 12 heads, by the rule for pairs that
+# divide over no XCDs); the 16x16 output pass of 5 to 8 key tiles in large grids (90 x 300, 50 x
+# 500); 128 queries per block in the output pass (9 x 1900) or in both (17 x 1900) past two blocks
+# per CU. float32: the output pass in blocks of 64 queries (most), and of 128 where no CU has less
+# to do with these (64 x 500; 8 x 512, 8 heads under a window)
 SHAPES = [(2, 64, 4, 0, True), (2, 256, 4, 0, True), (2, 257, 4, 0, True), (1, 320, 4, 0, False),
           (2, 321, 4, 0, True), (1, 384, 8, 0, False), (2, 449, 4, 0, True), (1, 513, 4, 0, False),
           (2, 577, 4, 0, True), (2, 300, 4, 64, True), (2, 333, 4, 2, True), (1, 1057, 4, 256, False),
-          (64, 500, 8, 0, True), (9, 1900, 8, 0, True), (8, 512, 8, 64, True)]
+          (64, 500, 8, 0, True), (8, 1900, 8, 0, True), (43, 500, 12, 0, True), (90, 300, 4, 0, True),
+          (50, 500, 8, 0, True), (9, 1900, 8, 0, True), (17, 1900, 4, 0, True), (8, 512, 8, 64, True)]
 
 
 def _reference(Q, K, H, lens, heads, window):
