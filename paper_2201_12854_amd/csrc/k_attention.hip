@@ -1398,8 +1398,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MT == 
     }
 }
 
-// ------------------------------------------------------------------ score pass, streaming
-// Streaming score pass (rows longer than 8 key tiles): 128 queries per block, two 16-query
+// ------------------------------------------------------------------ score pass, streaming, float32
+// float32 rows longer than 8 key tiles: 128 queries per block, two 16-query
 // tiles per wave, so that every K fragment read from LDS feeds two MFMAs and the per-tile
 // work (tile loads and stores, barriers, lane swaps, partial stores) serves twice the
 // queries. Two sweeps over the visited tiles: per-lane row statistics, then the column
@@ -1417,19 +1417,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MT == 
 
 // S = Q K^T of two 16-query tiles: acc[m][s][i] = dot(query 16 m + 4 g + i, key 16 s + r16)
 // + init[m][i].
-__device__ __forceinline__ void score_tile_qk2(f32x4_t acc[2][4], const uint16_t* Ks, const QFrag<1> q[2], int r16,
-                                               int g, const f32x4_t init[2]) {
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const bf16x8_t b0 = *reinterpret_cast<const bf16x8_t*>(Ks + kv_at(16 * s + r16, 8 * g));
-    const bf16x8_t b1 = *reinterpret_cast<const bf16x8_t*>(Ks + kv_at(16 * s + r16, 32 + 8 * g));
-    acc[0][s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q[0].v[0], b0, init[0], 0, 0, 0);
-    acc[1][s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q[1].v[0], b0, init[1], 0, 0, 0);
-    acc[0][s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q[0].v[1], b1, acc[0][s], 0, 0, 0);
-    acc[1][s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q[1].v[1], b1, acc[1][s], 0, 0, 0);
-  }
-}
-
 __device__ __forceinline__ void score_tile_qk2(f32x4_t acc[2][4], const float* Ks, const QFrag<0> q[2], int r16,
                                                int g, const f32x4_t init[2]) {
 #pragma unroll
@@ -1447,21 +1434,19 @@ __device__ __forceinline__ void score_tile_qk2(f32x4_t acc[2][4], const float* K
 }
 
 // IMP: the column statistic, 0 max (Eq. 8-9), 1 mean, 2 median (every probability to acol).
-template <int BF, bool BAND, int IMP>
+template <bool BAND, int IMP>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_scores_stream(FwdParams p) {
-  using T = typename Elem<BF>::T;
-  constexpr int S = stride_of<BF>();
-  __shared__ __align__(16) T Ks[2][kTile * S];
+  __shared__ __align__(16) float Ks[2][kTile * kStrideF];
   // sweep 2: per tile (three in flight), per wave and lane row, the lane row's value of key
   // 16 s + r16 at [r16][s]
   __shared__ __align__(16) float cm[3][4][4][16][4];
   __shared__ int redo;
   const BlockCtx c = block_ctx_q<128>(p);
   if (c.tid == 0) redo = 0;  // seen behind the first sweep's barriers
-  const T* Qb = static_cast<const T*>(p.Q) + (int64_t)c.b * c.n * c.d_out + c.h * kDHead;
-  const T* Kb = static_cast<const T*>(p.K) + (int64_t)c.b * c.n * c.d_out + c.h * kDHead;
+  const float* Qb = static_cast<const float*>(p.Q) + (int64_t)c.b * c.n * c.d_out + c.h * kDHead;
+  const float* Kb = static_cast<const float*>(p.K) + (int64_t)c.b * c.n * c.d_out + c.h * kDHead;
   const int qw = __builtin_amdgcn_readfirstlane(c.qt * 128 + c.wave * 32);  // the wave's first query
-  QFrag<BF> qf[2];
+  QFrag<0> qf[2];
 #pragma unroll
   for (int m = 0; m < 2; ++m) load_qfrag(qf[m], Qb + (int64_t)min(qw + 16 * m + c.r16, c.n - 1) * c.d_out, c.g);
   // the lane's eight queries qw + 16 m + 4 g + i in slot 4 m + i; under a local window each
@@ -1501,9 +1486,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   // (sweep 2 combines the waves' values of tile t - 1 after iteration t's barrier).
   // `first` sees tile 0's scores (masked) before the loop.
   auto sweep = [&](const f32x4_t init[2], auto&& first, auto&& work) {
-    TileRegs kr = tile_load<BF>(Kb, c.d_out, 0, c.n, c.tid);
-    tile_store<BF>(kr, Ks[0], c.tid);
-    kr = tile_load<BF>(Kb, c.d_out, tile_at(c, min(1, nvis - 1)) * kTile, c.n, c.tid);
+    TileRegs kr = tile_load<0>(Kb, c.d_out, 0, c.n, c.tid);
+    tile_store<0>(kr, Ks[0], c.tid);
+    kr = tile_load<0>(Kb, c.d_out, tile_at(c, min(1, nvis - 1)) * kTile, c.n, c.tid);
     lds_barrier();
     f32x4_t accA[2][4], accB[2][4];
     score_tile_qk2(accA, Ks[0], qf, c.r16, c.g, init);
@@ -1512,10 +1497,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
       const int kt = tile_at(c, t);
       const int lim = c.len - kt * kTile;
       if (BAND ? !band_tile_inside(c, kt, qw, 32) : lim < kTile) mask(cur, kt, lim);  // tile-uniform
-      T* buf = Ks[(t + 1) & 1];
-      tile_store<BF>(kr, buf, c.tid);
+      float* buf = Ks[(t + 1) & 1];
+      tile_store<0>(kr, buf, c.tid);
       lds_barrier();
-      kr = tile_load<BF>(Kb, c.d_out, tile_at(c, min(t + 2, nvis - 1)) * kTile, c.n, c.tid);
+      kr = tile_load<0>(Kb, c.d_out, tile_at(c, min(t + 2, nvis - 1)) * kTile, c.n, c.tid);
       score_tile_qk2(nxt, buf, qf, c.r16, c.g, init);
       work(cur, t, kt);
     };
@@ -2136,11 +2121,11 @@ template <bool BAND>
 hipError_t launch_scores_stream(const FwdParams& p, hipStream_t s) {
   const dim3 grid((unsigned)(p.qtiles * p.H * p.B)), blk(kThreads);
   if constexpr (BAND) {  // the mean and median rules are defined for full attention only
-    return launch_stage_kernel((k_scores_stream<0, true, 0>), grid, blk, 0, s, p);
+    return launch_stage_kernel((k_scores_stream<true, 0>), grid, blk, 0, s, p);
   } else {
-    if (p.importance == 1) return launch_stage_kernel((k_scores_stream<0, false, 1>), grid, blk, 0, s, p);
-    if (p.importance == 2) return launch_stage_kernel((k_scores_stream<0, false, 2>), grid, blk, 0, s, p);
-    return launch_stage_kernel((k_scores_stream<0, false, 0>), grid, blk, 0, s, p);
+    if (p.importance == 1) return launch_stage_kernel((k_scores_stream<false, 1>), grid, blk, 0, s, p);
+    if (p.importance == 2) return launch_stage_kernel((k_scores_stream<false, 2>), grid, blk, 0, s, p);
+    return launch_stage_kernel((k_scores_stream<false, 0>), grid, blk, 0, s, p);
   }
 }
 
