@@ -81,13 +81,36 @@ def upload(L, dev):
     return t
 
 
+def block_rules(L):
+    """(queries per block of the score pass, queries per block of the output pass, the output pass on
+    32x32 tiles): the launch code's rules, from the blocks that the CU with the most gets."""
+    import torch
+
+    nt, n128, pairs, bf = (L.seq + 63) // 64, (L.seq + 127) // 128, L.heads * L.batch, L.dtype == "bf16"
+    cus = torch.cuda.get_device_properties(0).multi_processor_count if torch.cuda.is_available() else 256
+    per_cu = lambda blocks: -(-blocks // cus)  # noqa: E731
+    score, out, tiles32 = 128 if nt > 8 else 64, 128, False
+    if nt <= (4 if bf else 2):
+        return 64, 64, False
+    c128, c256 = per_cu(n128 * pairs), per_cu((n128 + 1) // 2 * pairs)
+    if not bf:
+        return score, 64 if per_cu(nt * pairs) < 2 * c128 else 128, False
+    wide = not L.window and (n128 + 1) // 2 * pairs >= 2 * cus and (n128 % 2 == 0 or n128 >= 15)
+    if nt > 8 and wide and 3 * c128 >= 5 * c256:
+        score = 256
+    if wide and (pairs % 8 and L.seq <= 1024 or (c128 >= 2 * c256 if L.seq <= 512 else 4 * c128 >= 7 * c256)):
+        out = 256
+    return score, out, bool(L.window) or nt > 8 or out == 256 or c128 < 5
+
+
 def kernel_name(stage, L):
-    """The kernel a stage launches for this layer (the launch code's choice by padded length)."""
+    """The kernel a stage launches for this layer (the launch code's choice)."""
     nt = (L.seq + 63) // 64
+    resident = nt <= (4 if L.dtype == "bf16" else 2)
     if stage == "scores_colmax":
-        return "k_scores_res" if nt <= (4 if L.dtype == "bf16" else 2) else "k_scores_rs" if nt <= 8 else "k_scores_stream32" if L.dtype == "bf16" else "k_scores_stream"
+        return "k_scores_res" if resident else "k_scores_rs" if nt <= 8 else "k_scores_stream32" if L.dtype == "bf16" else "k_scores_stream"
     if stage == "attn_out":
-        return "k_attn_res" if nt <= (4 if L.dtype == "bf16" else 2) else "k_attn_stream32" if L.dtype == "bf16" and (nt > 5 or L.window) else "k_attn_stream"
+        return "k_attn_res" if resident else "k_attn_stream32" if block_rules(L)[2] else "k_attn_stream"
     return {"sample": "k_sample", "gather": "k_gather", "saturated": "k_saturated_lds"}[stage]
 
 
@@ -108,8 +131,7 @@ def stage_work(L, r, idx):
     B, n, d_in, d_out, H = L.batch, L.seq, L.d_in, L.d_out, L.heads
     elem = 4 if L.dtype == "f32" else 2
     lens = L.lens.astype(np.int64)
-    qt = 128 if (n + 63) // 64 > 8 else 64
-    nparts = H * ((n + qt - 1) // qt)
+    nparts = H * -(-n // block_rules(L)[0])  # column statistic partials per token
     sampled = (r > 0) & (r < d_in)
     sat = r == d_in
     distinct = 0
@@ -141,7 +163,7 @@ def stage_work(L, r, idx):
 
 
 def flop_reduction(L, r):
-    """X W_v multiply-adds, dense over sampled (the benchmark spec's figure), and the paper's ratio of
+    """X W_v multiply-adds, dense over sampled, and the paper's ratio of
     attention FLOPs A X W (Sec. Experiments: only the attention's FLOPs are counted)."""
     lens = L.lens.astype(np.float64)
     tot = float(np.sum(r))
