@@ -1690,8 +1690,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 // with the other waves' through LDS. Its accumulators start at -c / s. A slot is one MFMA and
 // two of the maxima.
 //
-// What bounds it: at 4096 tokens the power limit (the clock falls to about 1.7 GHz), so that
-// LDS reads and tile loads count beside the arithmetic: 64 queries per wave share them. K tiles
+// What bounds it: issue on the SIMDs, and at 4096 tokens the clock, which the card lowers under
+// this work (2.1 GHz reported over 5 s of passes, 2.4 in BERT-base layers), so that LDS reads and
+// tile loads count beside the arithmetic: 64 queries per wave share them. K tiles
 // take four buffers and load two iterations ahead, through the end of one sweep into the next.
 template <bool BAND, int IMP, int MT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_scores_stream32(FwdParams p) {

@@ -1,6 +1,7 @@
-"""Every direct load to LDS in the built library stands at least one instruction behind the last
-write of M0, its LDS address: gfx950 needs one wait state between the two, and inline assembly
-gets none from the compiler. Read from the library's own gfx950 code."""
+"""Every direct load to LDS in the built library keeps the wait states that gfx950 asks for and that
+inline assembly does not get from the compiler: one behind a write of M0, its LDS address, and five
+behind a vector instruction's write of a scalar register that it reads. Read from the library's own
+gfx950 code."""
 import os
 import re
 import shutil
@@ -38,9 +39,18 @@ def _code_objects(path):
         at = data.find(MAGIC, at + len(MAGIC))
 
 
-def _writes_m0(line):
-    op, _, args = line.partition(" ")
-    return op.startswith("s_") and args.split(",")[0].strip() == "m0"
+def _scalars(operands):
+    """The scalar registers named in a list of operands."""
+    regs = {"m0"} if re.search(r"\bm0\b", operands) else set()
+    for a, b in re.findall(r"\bs\[(\d+):(\d+)\]", operands):
+        regs.update(range(int(a), int(b) + 1))
+    regs.update(int(a) for a in re.findall(r"\bs(\d+)\b", operands))
+    return regs
+
+
+def _wait_states(line):
+    op, _, arg = line.partition(" ")
+    return int(arg) + 1 if op == "s_nop" else 1
 
 
 def test_m0_wait_state(tmp_path):
@@ -53,17 +63,24 @@ def test_m0_wait_state(tmp_path):
         f = tmp_path / f"{i}.co"
         f.write_bytes(obj)
         text = subprocess.run([tool, "-d", "--no-show-raw-insn", str(f)], capture_output=True, text=True, check=True).stdout
-        kernel, before = "", ""
+        kernel, before = "", []
         for line in text.splitlines():
             label = re.match(r"[0-9a-f]+ <(.*)>:", line)
             if label:
-                kernel, before = label.group(1), ""
+                kernel, before = label.group(1), []
                 continue
             line = line.split("//")[0].strip()
             if not line:
                 continue
             if re.match(r"(global_load_lds|buffer_load\w* .*\blds$)", line):
                 loads += 1
-                assert not _writes_m0(before), (kernel, before, line)
-            before = line
+                states, reads = 0, _scalars(line) | {"m0"}
+                for b in reversed(before):
+                    written = _scalars(b.partition(" ")[2].split(",")[0])
+                    assert states >= 1 or "m0" not in written, (kernel, b, line)
+                    assert not (b.startswith("v_") and written & reads), (kernel, b, line)
+                    states += _wait_states(b)
+                    if states >= 5:
+                        break
+            before = before[-8:] + [line]
     assert loads >= 10  # the streaming passes and the saturated tokens' kernels
